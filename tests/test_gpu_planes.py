@@ -66,8 +66,14 @@ def test_row_product_of_many_rows(ctx, n, k, m):
     assert bool(((out - ref).abs() <= _bound(a.double(), w.double())).all())
 
 
+def _bound_wide(a, w):
+    """... where a row or a column spans more than the planes hold: one fp32 chain over k."""
+    return _bound(a, w) + a.shape[1] * 2.0**-24 * (a.abs() @ w.abs())
+
+
 def test_outliers_and_extreme_magnitudes(ctx):
-    """One huge value in a row, rows and columns at both ends of the exponent range, denormal and zero rows."""
+    """One huge value in a row, rows and columns at both ends of the exponent range, denormal and zero rows.  (The bound of
+    an element is that of the terms it has: a huge value that meets a zero or a tiny weight leaves none.)"""
     import torch
 
     g = torch.Generator(device="cuda").manual_seed(3)
@@ -82,9 +88,80 @@ def test_outliers_and_extreme_magnitudes(ctx):
     w[:, 0] *= 1e-30
     w[:, 1] = 0.0
     w[3, 2] = 1e-38
+    w[5, 3:60] = 0.0
+    w[5, 60:] *= 1e-30
+    a[5, 6] = 1e34
+    w[6, 4] = 1e-38
+    a[:, 7] = torch.where(torch.arange(n, device="cuda") % 3 == 0, 1e-44, 0.0)
+    w[7, 8] = 1e30
     out = ctx.gcn_transform(a, w, None, None, relu=False).double()
     ref = a.double() @ w.double()
-    assert bool(((out - ref).abs() <= _bound(a.double(), w.double()) + 1e-42).all())
+    assert bool(((out - ref).abs() <= _bound_wide(a.double(), w.double()) + 1e-42).all())
+
+
+# one feature of another magnitude than the rest (a raw time stamp, a byte count) over weights that make up for it, over
+# zero weights (a feature that is not used), over weights that are zero for all but one column, and the mirrored case (one
+# tiny row of weights under features that make up for it); whole and ragged tiles, one and several row tiles per wave
+@pytest.mark.parametrize("exponent", [16, 24, 30, 40, 100])
+@pytest.mark.parametrize("n,k,m,bf16", [(65, 100, 64, False), (33, 260, 40, False), (129, 72, 200, True), (40, 100, 16, False)])
+def test_features_of_unequal_magnitudes(ctx, exponent, n, k, m, bf16):
+    import torch
+
+    assert _prepared(n, k, m) or m == 16
+    f = 2.0**exponent
+    for case in ("scaled", "zero", "one column", "tiny weight", "columns"):
+        g = torch.Generator(device="cuda").manual_seed(n + exponent)
+        a, w = torch.randn(n, k, generator=g, device="cuda"), torch.randn(k, m, generator=g, device="cuda")
+        b = torch.randn(m, generator=g, device="cuda")
+        if case == "tiny weight":
+            a[:, 3] *= 2.0 ** (0.7 * exponent)
+            w[3] /= f
+        elif case == "columns":  # a column of weights that spans as much, and features that are zero under its large part
+            w[:, 5] *= torch.exp2(-exponent * torch.rand(k, generator=g, device="cuda"))
+            a[:, w[:, 5].abs() > 0.01] = 0.0
+        else:
+            a[::2, 3] *= f  # (every other row: the others keep their results bit for bit)
+            w[3] = w[3] / f if case == "scaled" else 0.0
+            if case == "one column":
+                w[3, 7] = 1.0
+        a = a.bfloat16() if bf16 else a
+        rs = torch.rand(n, generator=g, device="cuda") + 0.01
+        out = ctx.gcn_transform(a, w, b, rs, relu=False)
+        scaled = (a.float() * rs[:, None]).double()
+        ref = scaled @ w.double() + b.double()
+        assert bool(((out.double() - ref).abs() <= _bound_wide(scaled, w.double()) + 2.0**-23 * ref.abs()).all()), case
+        if case == "zero":
+            a[::2] = a[1::2][:1]
+            assert torch.equal(ctx.gcn_transform(a, w, b, rs, relu=False)[1::2], out[1::2])
+
+
+# a few elements far below the rest of their row or column: as many as the lists take (8 and 4), one more, and elements too
+# small for them; the outputs that only those elements reach have to be right too
+@pytest.mark.parametrize("count", [1, 3, 4, 5, 8, 9])
+@pytest.mark.parametrize("exponent", [23, 40, 61, 90])
+@pytest.mark.parametrize("n,k,m", [(70, 100, 40), (33, 260, 130), (129, 72, 300)])
+def test_few_tiny_elements(ctx, count, exponent, n, k, m):
+    import torch
+
+    assert _prepared(n, k, m)
+    g = torch.Generator(device="cuda").manual_seed(count + exponent)
+    a, w = torch.randn(n, k, generator=g, device="cuda"), torch.randn(k, m, generator=g, device="cuda")
+    f = 2.0**-exponent
+    low = torch.randperm(k, generator=g, device="cuda")[:count]
+    rows = torch.arange(0, n, 3, device="cuda")
+    a[rows[:, None], low] *= f
+    keep = torch.zeros(k, dtype=torch.bool, device="cuda")
+    keep[low] = True
+    w[~keep, 1::4] = 0.0  # columns that only meet the rows' tiny elements
+    w[low[0], 2::4] *= f  # one tiny element in a column, `count` of them in others
+    w[:, 3::4][keep] *= f
+    a[1::3, ~keep] = 0.0  # rows that only meet those
+    b = torch.randn(m, generator=g, device="cuda") * f
+    out = ctx.gcn_transform(a, w, None, None, relu=False).double()
+    ref = a.double() @ w.double()
+    assert bool(((out - ref).abs() <= _bound_wide(a.double(), w.double())).all())
+    out = ctx.gcn_transform(a, w, b, None, relu=True).double()
+    assert bool(((out - torch.relu(ref + b.double())).abs() <= _bound_wide(a.double(), w.double()) + 2.0**-23 * b.abs()).all())
 
 
 def test_non_finite_rows_stay_in_their_rows(ctx):
@@ -145,6 +222,99 @@ def test_recurrent_step_edges(ctx, kind, n, d, h, zero_state):
         assert_close(c_out.cpu().numpy(), ref_c, RTOL_FP32, "c")
     assert_close(h_out.cpu().numpy(), ref_h, RTOL_FP32, "h")
     assert_close(saved.cpu().numpy(), np.concatenate(gates, axis=1), RTOL_FP32, "saved gates")
+
+
+# one feature of the input far above the rest over small or zero weights, an input far above the state, and a row of W_h far
+# above the rest under a zero state of that unit
+@pytest.mark.parametrize("kind", ["gru", "lstm"])
+@pytest.mark.parametrize("n,d,h", [(65, 100, 40), (8193, 128, 128), (33, 256, 256)])
+@pytest.mark.parametrize("case", ["scaled", "zero", "x over h", "W_h row", "few", "few, zero state"])
+def test_recurrent_step_of_unequal_magnitudes(ctx, kind, n, d, h, case):
+    import torch
+
+    from paper_2501_15348_amd import reinc
+
+    assert reinc._rnn_work_bytes(reinc.RNN[kind], n, d, h) > 0
+    rng = np.random.default_rng(n + d)
+    kg = 3 if kind == "gru" else 4
+    x, hp, cp = (rng.standard_normal((n, w)).astype(np.float32) for w in (d, h, h))
+    wi = (rng.standard_normal((d, kg * h)) / np.sqrt(d)).astype(np.float32)
+    wh = (rng.standard_normal((h, kg * h)) / np.sqrt(h)).astype(np.float32)
+    bi, bh = (rng.standard_normal(kg * h).astype(np.float32) * 0.3 for _ in range(2))
+    f = np.float32(2.0**34)
+    if case in ("scaled", "zero"):
+        x[::3, 2] *= f
+        wi[2] = wi[2] / f if case == "scaled" else 0.0
+    elif case == "x over h":
+        x *= f
+        wi /= f
+    elif case == "W_h row":
+        wh[3] *= f
+        hp[:, 3] = 0.0
+    else:  # a few tiny elements: inputs, states, weights of either part
+        x[::3, 4:6] /= f
+        hp[1::3, 1] /= f
+        wi[7, ::2] /= f
+        wh[2:4, ::3] /= f
+        wi[:, 5], x[:, 3] = 0.0, 0.0
+        wi[3, 5] = 1.0  # (with the line above: a column whose input part comes from its tiny terms alone)
+        if case == "few, zero state":
+            hp[:], cp[:] = 0.0, 0.0
+    dev = lambda v: torch.from_numpy(v).cuda()  # noqa: E731
+    saved = torch.empty((n, 4 * h), device="cuda")
+    state = (None, None) if case == "few, zero state" else (dev(hp), dev(cp) if kind == "lstm" else None)
+    h_out, c_out = ctx.rnn_step(kind, dev(x), *state, dev(wi), dev(wh), dev(bi), dev(bh), saved)
+    up = lambda v: v.astype(np.float64)  # noqa: E731
+    if kind == "gru":
+        ref_h, gates = oracle.gru_cell(up(x), up(hp), up(wi), up(wh), up(bi), up(bh))
+    else:
+        ref_h, ref_c, gates = oracle.lstm_cell(up(x), up(hp), up(cp), up(wi), up(wh), up(bi), up(bh))
+        assert np.abs(c_out.cpu().numpy() - ref_c).max() < 2e-5
+    # sums of at most 512 terms whose magnitudes add up to about 20: 512 * 2^-24 * 20 < 1e-3 in the worst case, a hundredth
+    # of it seen; a lost state or input shows as 0.1 to 1
+    assert np.abs(h_out.cpu().numpy() - ref_h).max() < 2e-5
+    assert np.abs(saved.cpu().numpy() - np.concatenate(gates, axis=1)).max() < 4e-5
+
+
+# a loss that is 2^36 times as large for one hidden unit, whose gates take nothing from the other units' weights: the other
+# units' gradients come from elements far below the largest of their rows
+@pytest.mark.parametrize("rnn", ["gru", "lstm"])
+@pytest.mark.parametrize("n,hidden", [(65, 40), (70, 64), (33, 128), (40, 136)])
+def test_backward_step_of_unequal_magnitudes(rnn, n, hidden):
+    import torch
+
+    from helpers import oracle_feats, oracle_graphs
+    from paper_2501_15348_amd import reinc, synth
+
+    length = 3
+    wl = synth.WORKLOADS["c3"].scaled(n, length, dims=(16, 48), hidden=hidden, rnn=rnn, mean_degree=4.0)
+    seq = synth.make_sequence(wl)
+    ctx = reinc.Context.for_workload(wl, arena_bytes=1 << 26)
+    ctx.load_sequence(seq)
+    ctx.build_deltas(-1)
+    flat, target = synth.make_params(wl, bias_scale=0.2), synth.make_target(wl)
+    target[:, 0] *= 2.0**36
+    p = synth.split_params(wl, flat)
+    kg = 3 if rnn == "gru" else 4
+    mine = np.arange(kg) * hidden  # the columns of unit 0
+    p["W_i"][:, mine] = 0.0
+    p["W_h"][:, mine] = 0.0
+    p["W_h"][0, :] = 0.0
+    flat = np.concatenate([p[name].ravel() for name, _ in synth.param_shapes(wl)]).astype(np.float32)
+    params, tgt = torch.from_numpy(flat).cuda(), torch.from_numpy(target).cuda()
+    loss, grads = torch.zeros(1, device="cuda"), torch.empty_like(params)
+    ctx.forward_window(0, length, params, tgt, loss)
+    ctx.backward_window(0, length, params, tgt, grads)
+    p = synth.split_params(wl, flat.astype(np.float64))
+    graphs, feats = oracle_graphs(seq), [oracle_feats(seq, t) for t in range(length)]
+    _, ref_h, saved = oracle.forward_window(graphs, feats, p, 1, wl.agg, wl.self_loop, rnn, target.astype(np.float64), keep=True)
+    ref = oracle.backward_window(graphs, saved, ref_h, p, 1, wl.agg, wl.self_loop, rnn, target.astype(np.float64))
+    got = synth.split_params(wl, grads.cpu().numpy())
+    for name in ("W_i", "W_h", "b_i", "b_h"):
+        for others in (False, True):
+            pick = (lambda v: np.delete(v, mine, axis=-1)) if others else (lambda v: v[..., mine])
+            assert_close(pick(got[name]), pick(ref[name]), 1e-3, f"{name}, {'other units' if others else 'unit 0'}")
+    ctx.close()
 
 
 # one backward step per launch: hidden widths around the two block shapes (64 and 128 units), with padded k-steps (three or
