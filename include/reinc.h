@@ -249,7 +249,9 @@ int reinc_rnn_step_work(reinc_ctx *ctx, int rnn_kind, const float *x, int64_t n,
  * from a zero state.  The layer-1 sums S_t of the stored features are weight-independent; they are kept in
  * the global cache for every t once computed (by Eq. 2 from S_{t-1} when that is cached and the step is under
  * fallback_ratio, else by Eq. 1) and reused by every later window.  Per-window activations go to the local
- * cache and stay there until the next forward call.  target: device [N, H] or NULL;
+ * cache and stay there until the next forward call.  A forward call uses no arena memory that a later call on another
+ * stream could take (node batches: none but their degree scales), and its results do not depend on the arena's size; the
+ * depth of the backward pass's batches and the form of its weights do, its gradients agree within fp32 rounding.  target: device [N, H] or NULL;
  * loss_out: device scalar = mean((h_last - target)^2) (ignored if target is NULL); h_last: device [N, H] or NULL. */
 int reinc_forward_window(reinc_ctx *ctx, int32_t t0, int32_t L, const float *params, const float *target,
                          float *loss_out, float *h_last, void *stream);

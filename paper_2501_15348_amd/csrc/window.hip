@@ -41,35 +41,24 @@ void rnn_backward_elem(reinc_ctx *ctx, hipStream_t st, A... a)
     launch_rnn_backward_elem(a..., st);
 }
 
-// The weights of one window call in matrix-core form.  They live in the call's scratch memory and are prepared by one
-// launch; where the arena has no room for them, or for a product that is too deep, the job stays empty and the product
-// takes the kernels that read the weights as they are.
+// The weights of one window call in matrix-core form, prepared by one launch.  A product whose job stays empty (no memory
+// for it, too deep, or a shape that gains nothing) takes the kernels that read the weights as they are.
 struct Planes {
     PlaneJobs jobs{};
-    uint64_t reserve = 0;  // arena bytes the call still has to allocate: they come first
-    // returns the index of the job, or -1
-    int add(reinc_ctx *ctx, const float *W1, const float *W2, int K1, int K2, int ldw, int wT, int gates, int width)
+    static bool wanted(int K1, int K2, int width)
     {
-        if (!dense_split_enabled() || !(K2 > 0 ? planes_pay_rnn(1, K1, K2, false) : planes_pay_backward(1, K1, width)) || jobs.count == kMaxPlaneJobs) return -1;
-        const uint64_t bytes = planes_bytes(K1, K2, gates, width);
-        if (ctx->bottom + reserve + bytes + 256 > ctx->top) return -1;
-        void *mem = ctx->scratch(bytes);
-        if (!mem) return -1;
+        return dense_split_enabled() && (K2 > 0 ? planes_pay_rnn(1, K1, K2, false) : planes_pay_backward(1, K1, width));
+    }
+    // returns the index of the job, or -1; mem: planes_bytes of it, or null
+    int add(void *mem, const float *W1, const float *W2, int K1, int K2, int ldw, int wT, int gates, int width)
+    {
+        if (!mem || !wanted(K1, K2, width) || jobs.count == kMaxPlaneJobs) return -1;
         jobs.job[jobs.count] = plane_job(W1, W2, K1, K2, ldw, wT, gates, width, mem);
         return jobs.count++;
     }
     const PlaneJob *get(int i) const { return i >= 0 ? &jobs.job[i] : nullptr; }
     void prepare(hipStream_t s) const { launch_prepare_planes(jobs, s); }
 };
-
-// arena bytes that the layer-1 sums of the window [t0, t0 + L) will take when they are computed
-uint64_t missing_layer1_bytes(const reinc_ctx *ctx, int32_t t0, int32_t L)
-{
-    if (ctx->gpolicy) return 0;  // (a budget's buffers are taken from the arena before)
-    uint64_t missing = 0;
-    for (int32_t t = t0; t < t0 + L; ++t) missing += ctx->gcache[t] == nullptr;
-    return missing * ((uint64_t(ctx->cached_rows()) * ctx->cfg.dims[0] * 4 + 255) & ~uint64_t(255));
-}
 
 // out[n,M] = epilogue((row_scale .* A)[n,K] * B[K,M]) with B = W or W^T, prepared (w) or not
 void product(reinc_ctx *ctx, hipStream_t st, const PlaneJob *w, const float *A, int64_t n, int K, int M, const float *row_scale,
@@ -248,6 +237,37 @@ void place_rows(reinc_ctx *ctx, hipStream_t s)
         ctx->local_top = nt;
     }
 }
+
+// Where a forward call keeps the weights of its recurrent steps in matrix-core form: memory of the local cache that the
+// call itself has no use for, so that neither another stream's loads (whose scratch memory begins right below the local
+// cache) nor a graph's replay after the arena has grown can meet it, and the kernels that a window takes depend on its
+// shape alone.  That is the zero state in front of the window (read by the backward pass: it is zero again when the call
+// is done), or what the placement of fewer rows leaves of the states' array.  Windows of a few hundred rows have neither.
+struct ForwardPlanes {
+    void *mem = nullptr;
+    int64_t zero_floats = 0;
+    float *zero_state;
+    hipStream_t s;
+    // rows: of a state as placed; d_in: width of the recurrent cell's input
+    ForwardPlanes(reinc_ctx *ctx, uint64_t rows, int d_in, hipStream_t stream) : zero_state(ctx->zero_state), s(stream)
+    {
+        const uint64_t H = uint64_t(ctx->cfg.rnn_hidden), slices = ctx->local.size() + 1;
+        if (!Planes::wanted(d_in, int(H), int(H))) return;
+        const uint64_t bytes = planes_bytes(d_in, int(H), ctx->cfg.rnn_kind == REINC_RNN_LSTM ? 4 : 3, int(H));
+        const uint64_t placed = slice_floats(rows, H) * 4, whole = slice_floats(uint64_t(ctx->cfg.num_nodes), H) * 4;
+        if (bytes <= placed) {
+            mem = zero_state;
+            zero_floats = int64_t(bytes / 4);
+        } else if (align256(slices * placed) + bytes <= slices * whole) {
+            mem = reinterpret_cast<char *>(zero_state) + align256(slices * placed);
+        }
+    }
+    ForwardPlanes(const ForwardPlanes &) = delete;
+    ~ForwardPlanes()
+    {
+        if (zero_floats > 0) launch_fill_f32(zero_state, zero_floats, 0.0f, s);
+    }
+};
 
 // dst[i * rows + r] = src_i[r] for the timesteps i of a batch: the degree scales of a layer that works on its first
 // rows only, next to each other like the layer's other per-timestep quantities
@@ -614,9 +634,9 @@ int reinc_forward_window(reinc_ctx *ctx, int32_t t0, int32_t L, const float *par
     // (one launch instead of one per timestep), the aggregation of a layer takes the batch's snapshots in one
     // launch; only the layer-1 sums (a chain over snapshots) and the recurrent cell (a chain over time) go
     // timestep by timestep.
+    ForwardPlanes room(ctx, uint64_t(nt), c.dims[Lg], s);
     Planes planes;
-    planes.reserve = missing_layer1_bytes(ctx, t0, L);
-    const int plane_rnn = planes.add(ctx, p.W_i, p.W_h, c.dims[Lg], H, (lstm ? 4 : 3) * H, 0, lstm ? 4 : 3, H);
+    const int plane_rnn = planes.add(room.mem, p.W_i, p.W_h, c.dims[Lg], H, (lstm ? 4 : 3) * H, 0, lstm ? 4 : 3, H);
     planes.prepare(s);
     std::vector<const float *> s1(L), q(L), ql(L), Hp(L), Sp(L), Hout(L);
     for (int32_t lo = 0; lo < L; lo += ctx->max_batch) {
@@ -712,7 +732,6 @@ int reinc_forward_window(reinc_ctx *ctx, int32_t t0, int32_t L, const float *par
     if (target) launch_mse(last.h, target, ctx->counted_rows() * H, ctx->loss_partial, loss_out, s);
     if (h_last) REINC_HIP(ctx, hipMemcpyAsync(h_last, last.h, uint64_t(nt) * H * 4, hipMemcpyDeviceToDevice, s));
     REINC_HIP(ctx, hipGetLastError());
-    ctx->scratch_reset();  // (what comes next may use the room again, in stream order)
     ctx->local_valid = true;
     ctx->local_t0 = t0;
     ctx->local_len = L;
@@ -753,14 +772,31 @@ int reinc_backward_window(reinc_ctx *ctx, int32_t t0, int32_t L, const float *pa
     float *dh = f32(uint64_t(n) * H), *dh2 = f32(uint64_t(n) * H);
     float *dc = lstm ? f32(uint64_t(n) * H) : nullptr, *dc2 = lstm ? f32(uint64_t(n) * H) : nullptr;
     bool ok = dh && dh2 && (!lstm || (dc && dc2));
-    const uint64_t free_bytes = ok ? ctx->top - ctx->bottom : 0;
+    // the degree scales of a batch of timesteps, next to each other, for a layer that works on its first rows only
+    int64_t scale_rows = 0;
+    if (c.agg_kind != REINC_AGG_SUM)
+        for (int l = 1; l <= Lg; ++l)
+            if (ctx->rows_of_layer(l) < n && !transform_first(c, l)) scale_rows = std::max(scale_rows, ctx->rows_of_layer(l));
     auto batch_bytes = [&](int B) {
         const uint64_t rows = uint64_t(B) * uint64_t(n);
-        uint64_t b = align256(rows * KH * 4) * (lstm ? 1 : 2) + 3 * align256(rows * maxd * 4);
+        uint64_t b = align256(uint64_t(B) * uint64_t(scale_rows) * 4);
+        b += align256(rows * KH * 4) * (lstm ? 1 : 2) + 3 * align256(rows * maxd * 4);
         b += align256(reduce_partial_bytes(int64_t(rows), c.dims[Lg], KH)) + align256(reduce_partial_bytes(int64_t(rows), H, KH));
         for (int l = 1; l <= Lg; ++l) b += align256(reduce_partial_bytes(int64_t(rows), c.dims[l - 1], c.dims[l]));
         return b + align256(column_sums_bytes(maxd));
     };
+    // the transposed weights come before the depth of a batch, but not before a batch of one timestep
+    Planes planes;
+    int plane_whT = -1, plane_wiT = -1, plane_wT[REINC_MAX_GCN_LAYERS + 1] = {-1, -1, -1, -1};
+    auto prepared = [&](const float *W, int K, int M) {  // W^T of a weight matrix W [M, K]
+        const uint64_t bytes = planes_bytes(K, 0, 1, M);
+        if (!ok || !Planes::wanted(K, 0, M) || batch_bytes(1) + align256(bytes) > ctx->top - ctx->bottom) return -1;
+        return planes.add(ctx->scratch(bytes), W, nullptr, K, 0, K, 1, 1, M);
+    };
+    plane_whT = prepared(p.W_h, KH, H);
+    plane_wiT = prepared(p.W_i, KH, c.dims[Lg]);
+    for (int l = 2; l <= Lg; ++l) plane_wT[l] = prepared(p.W[l], c.dims[l], c.dims[l - 1]);
+    const uint64_t free_bytes = ok ? ctx->top - ctx->bottom : 0;
     int B = std::min<int>(L, ctx->max_batch);
     while (B > 1 && batch_bytes(B) > free_bytes) --B;
     if (!ok || batch_bytes(B) > free_bytes) {
@@ -784,27 +820,15 @@ int reinc_backward_window(reinc_ctx *ctx, int32_t t0, int32_t L, const float *pa
     }
     float *colsum = static_cast<float *>(ctx->scratch(column_sums_bytes(maxd)));
     part_ok = part_ok && colsum;
-    // the degree scales of a batch of timesteps, next to each other, for a layer that works on its first rows only
     float *q_rows = nullptr;
-    if (c.agg_kind != REINC_AGG_SUM) {
-        int64_t most = 0;
-        for (int l = 1; l <= Lg; ++l)
-            if (ctx->rows_of_layer(l) < n && !transform_first(c, l)) most = std::max(most, ctx->rows_of_layer(l));
-        if (most > 0) {
-            q_rows = static_cast<float *>(ctx->scratch(uint64_t(B) * most * 4));
-            part_ok = part_ok && q_rows;
-        }
+    if (scale_rows > 0) {
+        q_rows = static_cast<float *>(ctx->scratch(uint64_t(B) * scale_rows * 4));
+        part_ok = part_ok && q_rows;
     }
     if (!dgi || !dgh || !dz || !dz2 || !dagg || !part_ok) {
         ctx->scratch_reset();
         return ctx->fail(REINC_E_NOMEM, "arena exhausted: no room for the backward scratch buffers");
     }
-    // the transposed weights, last: they get what the buffers above leave
-    Planes planes;
-    int plane_wT[REINC_MAX_GCN_LAYERS + 1] = {-1, -1, -1, -1};
-    const int plane_whT = planes.add(ctx, p.W_h, nullptr, KH, 0, KH, 1, 1, H);
-    const int plane_wiT = planes.add(ctx, p.W_i, nullptr, KH, 0, KH, 1, 1, c.dims[Lg]);
-    for (int l = 2; l <= Lg; ++l) plane_wT[l] = planes.add(ctx, p.W[l], nullptr, c.dims[l], 0, c.dims[l], 1, 1, c.dims[l - 1]);
     planes.prepare(s);
     launch_fill_f32(grads, p.count, 0.0f, s);
     launch_mse_grad(ctx->local[L - 1].h, target, ctx->counted_rows() * H, nt * H, dh, s);
@@ -1000,9 +1024,9 @@ int reinc_forward_window_integrated(reinc_ctx *ctx, int32_t t0, int32_t L, const
     const int64_t KH = int64_t(lstm ? 4 : 3) * H;
     const float *W_i = params, *W_h = W_i + int64_t(c.dims[0]) * KH, *b_i = W_h + int64_t(H) * KH, *b_h = b_i + KH;
     const float *nof = nullptr;
+    ForwardPlanes room(ctx, uint64_t(n), c.dims[0], s);
     Planes planes;
-    planes.reserve = missing_layer1_bytes(ctx, t0, L);
-    const int plane_rnn = planes.add(ctx, W_i, W_h, c.dims[0], H, int(KH), 0, lstm ? 4 : 3, H);
+    const int plane_rnn = planes.add(room.mem, W_i, W_h, c.dims[0], H, int(KH), 0, lstm ? 4 : 3, H);
     planes.prepare(s);
     ctx->step_rows.assign(size_t(L), n);
     for (int32_t i = 0; i < L; ++i) {
@@ -1031,7 +1055,6 @@ int reinc_forward_window_integrated(reinc_ctx *ctx, int32_t t0, int32_t L, const
     if (target) launch_mse(last.h, target, ctx->counted_rows() * H, ctx->loss_partial, loss_out, s);
     if (h_last) REINC_HIP(ctx, hipMemcpyAsync(h_last, last.h, uint64_t(n_last) * H * 4, hipMemcpyDeviceToDevice, s));
     REINC_HIP(ctx, hipGetLastError());
-    ctx->scratch_reset();  // (what comes next may use the room again, in stream order)
     ctx->local_valid = true;
     ctx->local_t0 = t0;
     ctx->local_len = L;
@@ -1062,12 +1085,17 @@ int reinc_backward_window_integrated(reinc_ctx *ctx, int32_t t0, int32_t L, cons
     float *dh = f32(uint64_t(n) * H), *dh2 = f32(uint64_t(n) * H), *dah = f32(uint64_t(n) * H);
     float *dc = lstm ? f32(uint64_t(n) * H) : nullptr, *dc2 = lstm ? f32(uint64_t(n) * H) : nullptr;
     bool ok = dh && dh2 && dah && (!lstm || (dc && dc2));
-    const uint64_t free_bytes = ok ? ctx->top - ctx->bottom : 0;
     auto batch_bytes = [&](int B) {
         const uint64_t rows = uint64_t(B) * uint64_t(n);
         return align256(rows * KH * 4) * (lstm ? 1 : 2) + align256(reduce_partial_bytes(int64_t(rows), d0, KH)) +
                align256(reduce_partial_bytes(int64_t(rows), H, KH));
     };
+    // the transposed weights come before the depth of a batch, but not before a batch of one timestep
+    Planes planes;
+    int plane_whT = -1;
+    if (const uint64_t bytes = planes_bytes(KH, 0, 1, H); ok && Planes::wanted(KH, 0, H) && batch_bytes(1) + align256(bytes) <= ctx->top - ctx->bottom)
+        plane_whT = planes.add(ctx->scratch(bytes), W_h, nullptr, KH, 0, KH, 1, 1, H);
+    const uint64_t free_bytes = ok ? ctx->top - ctx->bottom : 0;
     int B = std::min<int>(L, ctx->max_batch);
     while (B > 1 && batch_bytes(B) > free_bytes) --B;
     if (!ok || batch_bytes(B) > free_bytes) {
@@ -1083,8 +1111,6 @@ int reinc_backward_window_integrated(reinc_ctx *ctx, int32_t t0, int32_t L, cons
         ctx->scratch_reset();
         return ctx->fail(REINC_E_NOMEM, "arena exhausted: no room for the backward scratch buffers");
     }
-    Planes planes;  // (last: they get what the buffers above leave)
-    const int plane_whT = planes.add(ctx, W_h, nullptr, KH, 0, KH, 1, 1, H);
     planes.prepare(s);
     launch_fill_f32(grads, count, 0.0f, s);
     launch_mse_grad(ctx->local[L - 1].h, target, ctx->counted_rows() * H, n * H, dh, s);

@@ -345,3 +345,100 @@ def test_backward_step_edges(rnn, n, hidden):
                            lambda sv: oracle.backward_window(graphs, sv, ref_h, p, 1, wl.agg, wl.self_loop, rnn, target),
                            [name for name, _ in synth.param_shapes(wl)], GRAD_RTOL_FP32)
     ctx.close()
+
+
+# shapes with the recurrent weights in matrix-core form: in the zero state before the window (many rows), in what a node
+# batch's placement leaves of the states' array (covered by the batch tests), nowhere (40 rows)
+@pytest.mark.parametrize("model", ["stacked", "integrated"])
+@pytest.mark.parametrize("rnn,hidden,n", [("gru", 64, 3001), ("lstm", 128, 2500), ("lstm", 64, 40)])
+def test_window_weights_are_out_of_the_arenas_way(model, rnn, hidden, n):
+    """A forward call that waits on its own stream while the next snapshot is loaded (whose scratch memory and arrays take
+    the arena up to the local cache), and a captured one that is replayed after that, give what an undisturbed call gives;
+    so does a context whose arena has next to no room left."""
+    import torch
+
+    from paper_2501_15348_amd import reinc, synth
+
+    steps = 6
+    wl = synth.WORKLOADS["c2"].scaled(n, steps, dims=(64, 64), hidden=hidden, rnn=rnn)
+    seq = synth.make_sequence(wl)
+    params = torch.from_numpy(synth.make_params(wl, bias_scale=0.2)).cuda()
+    if model == "integrated":
+        params = params[-(64 + hidden + 2) * (3 if rnn == "gru" else 4) * hidden:].contiguous()
+    target = torch.from_numpy(synth.make_target(wl)).cuda()
+    xs = [seq.x0]
+    for t in range(1, steps):
+        x = xs[-1].copy()
+        x[seq.feat_rows[t]] = seq.feat_vals[t]
+        xs.append(x)
+
+    def load(ctx, t):
+        ctx.load_edges(t, *seq.edges[t])
+        ctx.load_features_full(t, xs[t])
+
+    def outputs():
+        return torch.zeros(1, device="cuda"), torch.zeros(n, hidden, device="cuda"), torch.zeros_like(params)
+
+    def run(ctx, loss, h, grads, backward=True):
+        (ctx.forward_window if model == "stacked" else ctx.forward_window_integrated)(0, 4, params, target, loss, h)
+        if backward:
+            (ctx.backward_window if model == "stacked" else ctx.backward_window_integrated)(0, 4, params, target, grads)
+
+    def context(arena):
+        ctx = reinc.Context.for_workload(wl, arena_bytes=arena)
+        for t in range(4):
+            load(ctx, t)
+        return ctx
+
+    ctx = context(1 << 28)
+    quiet = outputs()
+    run(ctx, *quiet)
+    used = (1 << 28) - ctx.arena_free_bytes()
+    torch.cuda.synchronize()
+    ctx.close()
+
+    # the arena as small as the window calls allow, found by halving: the forward pass takes the same kernels
+    low, high, tight = used // 4, 1 << 28, None
+    while high - low > 4096:
+        size = (low + high) // 2 // 256 * 256
+        got, small = outputs(), reinc.Context.for_workload(wl, arena_bytes=size)
+        try:
+            for t in range(4):
+                load(small, t)
+            run(small, *got)
+            torch.cuda.synchronize()
+            high, tight = size, got
+        except reinc.ReincError as e:
+            assert e.code == reinc.E_NOMEM
+            low = size
+        finally:
+            small.close()
+    assert torch.equal(tight[0], quiet[0]) and torch.equal(tight[1], quiet[1])
+    assert_close(tight[2].cpu().numpy(), quiet[2].cpu().numpy(), RTOL_FP32, "gradients in the smallest arena")
+
+    ctx = context(1 << 28)
+    side = torch.cuda.Stream()
+    busy = outputs()
+    run(ctx, *outputs(), backward=False)  # (the local cache and the layer-1 sums are made)
+    torch.cuda.synchronize()
+    graph, replayed = torch.cuda.CUDAGraph(), outputs()
+    with torch.cuda.graph(graph):
+        run(ctx, *replayed, backward=False)
+    with torch.cuda.stream(side):
+        torch.cuda._sleep(200_000_000)
+        run(ctx, *busy, backward=False)
+    load(ctx, 4)
+    load(ctx, 5)
+    torch.cuda.synchronize()
+    with torch.cuda.stream(side):
+        (ctx.backward_window if model == "stacked" else ctx.backward_window_integrated)(0, 4, params, target, busy[2])
+    torch.cuda.synchronize()
+    for a, b in zip(busy, quiet):
+        assert torch.equal(a, b)
+    for _ in range(3):
+        replayed[1].zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(replayed[0], quiet[0]) and torch.equal(replayed[1], quiet[1])
+    assert [ctx.get_snapshot_csr(t)[1].size for t in (4, 5)] == [len(set(zip(*map(np.ndarray.tolist, seq.edges[t])))) for t in (4, 5)]
+    ctx.close()
