@@ -34,8 +34,8 @@ def _bound(a, w):
 # K % 32 != 0: taken at any n; whole tiles and remainders of rows (64 or 32 per block), of columns (32 per tile, 1, 2, 4
 # and 8 tiles per pass), of k (padded to 32; one, two and four groups of eight per lane), and the deep products
 @pytest.mark.parametrize("n", [1, 31, 64, 65, 193])
-@pytest.mark.parametrize("k,m", [(65, 1), (100, 33), (66, 64), (72, 65), (200, 128), (250, 129), (33, 257), (510, 40), (512, 128),
-                                 (480, 300), (7, 96), (260, 32)])
+@pytest.mark.parametrize("k,m", [(65, 1), (100, 33), (66, 64), (72, 65), (200, 128), (250, 129), (49, 257), (510, 40), (512, 128),
+                                 (480, 300), (57, 96), (260, 32)])
 @pytest.mark.parametrize("bf16", [False, True])
 def test_row_product_edges(ctx, n, k, m, bf16):
     import torch
@@ -187,7 +187,7 @@ def test_shapes_that_keep_the_resident_kernels():
     reinc.load_library()
     for n, d, h in ((8191, 128, 128), (100000, 64, 96), (100000, 128, 32), (0, 16, 16), (100, 512, 32)):
         assert reinc._rnn_work_bytes(0, n, d, h) == 0, (n, d, h)
-    for n, k, m in ((100000, 32, 512), (30000, 256, 256), (98000, 128, 128), (0, 100, 100), (50, 513, 64)):
+    for n, k, m in ((100000, 32, 512), (50, 7, 96), (100000, 31, 64), (100000, 48, 512), (30000, 256, 256), (98000, 128, 128), (0, 100, 100), (50, 513, 64)):
         assert reinc._gcn_work_bytes(n, k, m) == 0, (n, k, m)
 
 
