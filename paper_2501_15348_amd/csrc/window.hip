@@ -45,14 +45,15 @@ void rnn_backward_elem(reinc_ctx *ctx, hipStream_t st, A... a)
 // for it, too deep, or a shape that gains nothing) takes the kernels that read the weights as they are.
 struct Planes {
     PlaneJobs jobs{};
-    static bool wanted(int K1, int K2, int width)
+    // rows: of a recurrent step (a backward product's rows differ from batch to batch: `product` looks again)
+    static bool wanted(int K1, int K2, int width, int64_t rows = 1)
     {
-        return dense_split_enabled() && (K2 > 0 ? planes_pay_rnn(1, K1, K2, false) : planes_pay_backward(1, K1, width));
+        return dense_split_enabled() && (K2 > 0 ? planes_pay_rnn(rows, K1, K2, false) : planes_pay_backward(rows, K1, width));
     }
-    // returns the index of the job, or -1; mem: planes_bytes of it, or null
+    // returns the index of the job, or -1; mem: planes_bytes of it, or null (not wanted, no room)
     int add(void *mem, const float *W1, const float *W2, int K1, int K2, int ldw, int wT, int gates, int width)
     {
-        if (!mem || !wanted(K1, K2, width) || jobs.count == kMaxPlaneJobs) return -1;
+        if (!mem || jobs.count == kMaxPlaneJobs) return -1;
         jobs.job[jobs.count] = plane_job(W1, W2, K1, K2, ldw, wT, gates, width, mem);
         return jobs.count++;
     }
@@ -252,7 +253,7 @@ struct ForwardPlanes {
     ForwardPlanes(reinc_ctx *ctx, uint64_t rows, int d_in, hipStream_t stream) : zero_state(ctx->zero_state), s(stream)
     {
         const uint64_t H = uint64_t(ctx->cfg.rnn_hidden), slices = ctx->local.size() + 1;
-        if (!Planes::wanted(d_in, int(H), int(H))) return;
+        if (!Planes::wanted(d_in, int(H), int(H), int64_t(rows))) return;
         const uint64_t bytes = planes_bytes(d_in, int(H), ctx->cfg.rnn_kind == REINC_RNN_LSTM ? 4 : 3, int(H));
         const uint64_t placed = slice_floats(rows, H) * 4, whole = slice_floats(uint64_t(ctx->cfg.num_nodes), H) * 4;
         if (bytes <= placed) {

@@ -53,11 +53,11 @@ def test_row_product_edges(ctx, n, k, m, bf16):
     assert bool(((out - ref).abs() <= _bound(scaled, w.double()) + 2.0**-23 * ref.abs()).all())
 
 
-@pytest.mark.parametrize("n,k,m", [(32768, 256, 128), (32801, 256, 256), (32801, 64, 512), (98305, 128, 128), (32768, 384, 160)])
+@pytest.mark.parametrize("n,k,m", [(65536, 256, 256), (65601, 256, 300), (98305, 128, 256), (98304, 224, 129), (65537, 384, 200)])
 def test_row_product_of_many_rows(ctx, n, k, m):
     import torch
 
-    assert _prepared(n, k, m) and not _prepared(n // 4, k, m)
+    assert _prepared(n, k, m) and not _prepared(n // 2, k, m)
     g = torch.Generator(device="cuda").manual_seed(n + k + m)
     a = torch.randn(n, k, generator=g, device="cuda")
     w = torch.randn(k, m, generator=g, device="cuda") / k**0.5
@@ -185,16 +185,16 @@ def test_shapes_that_keep_the_resident_kernels():
     from paper_2501_15348_amd import reinc
 
     reinc.load_library()
-    for n, d, h in ((8191, 128, 128), (100000, 64, 96), (100000, 128, 32), (0, 16, 16), (100, 512, 32)):
+    for n, d, h in ((32767, 128, 128), (100000, 64, 96), (100000, 64, 64), (100000, 64, 128), (100000, 128, 32), (0, 16, 16), (100, 512, 32)):
         assert reinc._rnn_work_bytes(0, n, d, h) == 0, (n, d, h)
-    for n, k, m in ((100000, 32, 512), (50, 7, 96), (100000, 31, 64), (100000, 48, 512), (30000, 256, 256), (98000, 128, 128), (0, 100, 100), (50, 513, 64)):
+    for n, k, m in ((100000, 32, 512), (50, 7, 96), (100000, 31, 64), (100000, 48, 512), (65535, 256, 256), (200000, 384, 128), (200000, 64, 512), (98303, 128, 256), (200000, 128, 128), (0, 100, 100), (50, 513, 64)):
         assert reinc._gcn_work_bytes(n, k, m) == 0, (n, k, m)
 
 
 # hidden units: one tile and a remainder, two tiles, more than four (a second pass), depths up to 512
 @pytest.mark.parametrize("kind", ["gru", "lstm"])
 @pytest.mark.parametrize("n,d,h,zero_state", [(1, 16, 16, False), (65, 33, 33, False), (129, 100, 64, True), (64, 64, 65, False),
-                                              (8193, 128, 128, False), (8192, 64, 64, True), (97, 96, 250, False), (33, 256, 256, False), (70, 1, 31, False),
+                                              (32769, 128, 128, False), (8192, 60, 64, True), (97, 96, 250, False), (33, 256, 256, False), (70, 1, 31, False),
                                               (40, 300, 40, True)])
 def test_recurrent_step_edges(ctx, kind, n, d, h, zero_state):
     import torch
@@ -227,7 +227,7 @@ def test_recurrent_step_edges(ctx, kind, n, d, h, zero_state):
 # one feature of the input far above the rest over small or zero weights, an input far above the state, and a row of W_h far
 # above the rest under a zero state of that unit
 @pytest.mark.parametrize("kind", ["gru", "lstm"])
-@pytest.mark.parametrize("n,d,h", [(65, 100, 40), (8193, 128, 128), (33, 256, 256)])
+@pytest.mark.parametrize("n,d,h", [(65, 100, 40), (32769, 128, 128), (33, 256, 256)])
 @pytest.mark.parametrize("case", ["scaled", "zero", "x over h", "W_h row", "few", "few, zero state"])
 def test_recurrent_step_of_unequal_magnitudes(ctx, kind, n, d, h, case):
     import torch
