@@ -393,7 +393,7 @@ int reinc_get_stats(reinc_ctx *ctx, reinc_stats *out);
 #define REINC_K_GEMM_ROWS 2  /* row-tile GEMM (GCN update, input gradients) */
 #define REINC_K_RNN 3        /* fused recurrent step */
 #define REINC_K_REDUCE 4     /* weight-gradient reduction GEMM */
-#define REINC_K_ELEM 5       /* elementwise recurrent backward */
+#define REINC_K_ELEM 5       /* recurrent backward: gate gradients, with their product with W_h^T where one launch does both */
 #define REINC_K_DIFF 6       /* snapshot-diff count + fill */
 #define REINC_K_AGG_MINMAX 7 /* max / min aggregation (from scratch or incremental: all kernels of a call) */
 #define REINC_K_COUNT 8

@@ -242,6 +242,11 @@ struct ProfScope {
     ~ProfScope() {
         if (slot >= 0 && !attached) (void)hipEventRecord(ctx->prof_events[2 * slot + 1], s);
     }
+    // nothing was launched after all
+    void drop() {
+        if (slot >= 0) ctx->prof_kind.pop_back();
+        slot = -1;
+    }
     hipEvent_t start() const { return slot >= 0 ? ctx->prof_events[2 * slot] : nullptr; }
     hipEvent_t stop() const { return slot >= 0 ? ctx->prof_events[2 * slot + 1] : nullptr; }
     ProfScope(const ProfScope &) = delete;

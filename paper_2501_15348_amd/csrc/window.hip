@@ -87,7 +87,9 @@ bool rnn_backward_step(reinc_ctx *ctx, hipStream_t st, const PlaneJob *whT, int 
 {
     if (!whT) return false;
     ProfScope prof(ctx, REINC_K_ELEM, st);
-    return launch_rnn_backward_planes(*whT, lstm, n, H, dh, dc, saved, h_prev, c_prev, c_new, dgi, dgh, dc_out, carry_out, out, st);
+    if (launch_rnn_backward_planes(*whT, lstm, n, H, dh, dc, saved, h_prev, c_prev, c_new, dgi, dgh, dc_out, carry_out, out, st)) return true;
+    prof.drop();
+    return false;
 }
 
 struct Params {
@@ -535,6 +537,7 @@ int reinc_gcn_transform_work(reinc_ctx *ctx, const void *A, int a_dtype, int64_t
             REINC_HIP(ctx, hipGetLastError());
             return REINC_OK;
         }
+        prof.drop();
     }
     gemm_rows(ctx, as_stream(stream), A, int(a_dtype == REINC_BF16), n, d_in, d_out, row_scale, W, 0, d_out, b, relu,
               (const float *)nullptr, (const float *)nullptr, out);
@@ -579,6 +582,7 @@ int reinc_rnn_step_work(reinc_ctx *ctx, int rnn_kind, const float *x, int64_t n,
             REINC_HIP(ctx, hipGetLastError());
             return REINC_OK;
         }
+        prof.drop();
     }
     rnn_fused(ctx, as_stream(stream), int(rnn_kind == REINC_RNN_LSTM), x, static_cast<const float *>(nullptr), n, d_in, H, h_prev,
               h_prev, c_prev, W_i, W_h, b_i, b_h, h_out, c_out, saved);

@@ -442,3 +442,23 @@ def test_window_weights_are_out_of_the_arenas_way(model, rnn, hidden, n):
         assert torch.equal(replayed[0], quiet[0]) and torch.equal(replayed[1], quiet[1])
     assert [ctx.get_snapshot_csr(t)[1].size for t in (4, 5)] == [len(set(zip(*map(np.ndarray.tolist, seq.edges[t])))) for t in (4, 5)]
     ctx.close()
+
+
+# one profiled launch per timestep of the backward recurrence, whether gate gradients and product share it (64 units, but
+# for the first timestep) or the width is not for that kernel (136, 44)
+@pytest.mark.parametrize("hidden,products", [(64, 0), (136, 2), (44, 2)])
+def test_profile_counts_launches_of_the_backward_recurrence_once(hidden, products):
+    import torch
+
+    from paper_2501_15348_amd import reinc, synth
+
+    wl = synth.WORKLOADS["c3"].scaled(200, 3, dims=(16, 32), hidden=hidden, rnn="gru", mean_degree=4.0)
+    ctx = reinc.Context.for_workload(wl, arena_bytes=1 << 26)
+    ctx.load_sequence(synth.make_sequence(wl))
+    params, tgt = torch.from_numpy(synth.make_params(wl)).cuda(), torch.from_numpy(synth.make_target(wl)).cuda()
+    ctx.forward_window(0, 3, params, tgt, torch.zeros(1, device="cuda"))
+    ctx.profile_begin(["elem", "gemm_rows"])
+    ctx.backward_window(0, 3, params, tgt, torch.empty_like(params))
+    seen = {k: v[0] for k, v in ctx.profile_end().items()}
+    assert seen["elem"] == 3 and seen["gemm_rows"] == products + 1, seen  # (and W_i^T's, all timesteps at once)
+    ctx.close()
