@@ -270,8 +270,9 @@ def main():
                    "dims": list(wl.dims), "rnn": wl.rnn, "hidden": wl.hidden, "fallback_ratio": 0.5,
                    "step": "build deltas + cold epoch of forward/backward/SGD over all windows",
                    "dense_products": ("fp32 matrix instructions" if os.environ.get("REINC_DENSE") == "fp32" else
-                                      "f32 operands as three bfloat16 terms each, six products on the bf16 matrix cores, "
-                                      "f32 accumulation (error as the fp32 instructions)")},
+                                      "f32 operands as three bfloat16 terms each, six products on the bf16 matrix cores, or as "
+                                      "two scaled fp16 terms each, three products on the fp16 matrix cores; f32 accumulation "
+                                      "(error as the fp32 instructions)")},
         "value_definition": "effective delta edges consumed by Eq. 2 steps in the timed region / summed duration of the "
                             "incremental kernel's launches in the timed region",
         "delta_edges_per_step": int(delta_edges), "delta_edges_through_eq2_per_step": int(consumed),
@@ -450,27 +451,36 @@ def extras(ctx, wl, seq, infos, params, target, step, step_s, full):
     return res
 
 
-MFMA_BF16_PEAK_TFLOPS = 2500.0  # dense bf16 matrix-core peak of MI355X
+MFMA_16BIT_PEAK_TFLOPS = 2500.0  # dense bf16 / fp16 matrix-core peak of MI355X
 MFMA_F32_PEAK_TFLOPS = 157.3
 
 
 def dense_rows(ctx, wl, timed):
     """K5 per GCN layer and K6 at the workload's row count, one timestep per call (inside a window the driver hands
     them up to MAX_BATCH timesteps as one taller matrix): algorithmic bytes against the HBM peak, and the matrix-core
-    rate -- fp32-equivalent flops, and the six bf16 products per fp32 product that the three-term split really
-    issues, against the bf16 peak.  With REINC_DENSE=fp32 the products run on the fp32 matrix instructions instead."""
+    rate -- fp32-equivalent flops, and the products that the call's kernel really issues per fp32 product (six bf16 ones of
+    the three-term split, three fp16 ones of the two-term split), against the 16-bit peak.  Shapes that the split
+    kernels leave alone, and all with REINC_DENSE=fp32, run on the fp32 matrix instructions instead."""
     import torch
 
     n = wl.num_nodes
-    split = os.environ.get("REINC_DENSE") != "fp32"
+    from paper_2501_15348_amd import reinc
+
+    def products(work_bytes, resident):
+        """Matrix products per fp32 product: fp16 planes (a work area), bf16 planes in LDS, or 0: fp32 instructions."""
+        if os.environ.get("REINC_DENSE") == "fp32":
+            return 0
+        return 3 if work_bytes else 6 if resident else 0
+
     g = torch.Generator(device="cuda").manual_seed(3)
 
-    def row(ms, nbytes, flops):
+    def row(ms, nbytes, flops, terms):
         r = {"us": round(ms * 1e3, 1), "algorithmic_GBps": round(nbytes / ms / 1e6, 1),
              "hbm_frac": round(nbytes / ms / 1e6 / HBM_PEAK_GBS, 4), "f32_equivalent_TFLOPs": round(flops / ms / 1e9, 1)}
-        if split:
-            r["bf16_products_TFLOPs"] = round(6 * flops / ms / 1e9, 1)
-            r["mfma_frac"] = round(6 * flops / ms / 1e9 / MFMA_BF16_PEAK_TFLOPS, 4)
+        if terms:
+            r["split_products"] = "3 fp16" if terms == 3 else "6 bf16"
+            r["split_products_TFLOPs"] = round(terms * flops / ms / 1e9, 1)
+            r["mfma_frac"] = round(terms * flops / ms / 1e9 / MFMA_16BIT_PEAK_TFLOPS, 4)
         else:
             r["mfma_frac"] = round(flops / ms / 1e9 / MFMA_F32_PEAK_TFLOPS, 4)
         return r
@@ -483,7 +493,8 @@ def dense_rows(ctx, wl, timed):
         b = torch.zeros(m, device="cuda")
         out = torch.empty(n, m, device="cuda")
         ms = timed(lambda: ctx.gcn_transform(a, w, b, None, True, out))
-        layers.append({"rows": n, "d_in": k, "d_out": m, **row(ms, n * (k + m) * 4 + k * m * 4, 2.0 * n * k * m)})
+        layers.append({"rows": n, "d_in": k, "d_out": m, **row(ms, n * (k + m) * 4 + k * m * 4, 2.0 * n * k * m,
+                                                                   products(reinc._gcn_work_bytes(n, k, m), k % 32 == 0 and k < 448))})
         del a, out
     d, h = wl.dims[-1], wl.hidden
     kg = 4 if wl.rnn == "lstm" else 3
@@ -497,7 +508,9 @@ def dense_rows(ctx, wl, timed):
     ms = timed(lambda: ctx.rnn_step(wl.rnn, x, hp, cp, wi, wh, bi, bh, saved))
     # x, h (and c) read; h (and c) and the four saved gate rows written
     nbytes = n * 4 * (d + h * (2 if cp is not None else 1) * 2 + 4 * h)
-    cell = {"rows": n, "d_in": d, "hidden": h, "kind": wl.rnn, **row(ms, nbytes, 2.0 * n * (d + h) * kg * h)}
+    cell = {"rows": n, "d_in": d, "hidden": h, "kind": wl.rnn, **row(ms, nbytes, 2.0 * n * (d + h) * kg * h,
+                                                                         products(reinc._rnn_work_bytes(reinc.RNN[wl.rnn], n, d, h),
+                                                                                  d % 32 == 0 and h % 32 == 0 and d + h <= 256))}
     return layers, cell
 
 
