@@ -187,7 +187,7 @@ def test_shapes_that_keep_the_resident_kernels():
     reinc.load_library()
     for n, d, h in ((32767, 128, 128), (100000, 64, 96), (100000, 64, 64), (100000, 64, 128), (100000, 128, 32), (0, 16, 16), (100, 512, 32)):
         assert reinc._rnn_work_bytes(0, n, d, h) == 0, (n, d, h)
-    for n, k, m in ((100000, 32, 512), (50, 7, 96), (100000, 31, 64), (100000, 48, 512), (65535, 256, 256), (200000, 384, 128), (200000, 64, 512), (98303, 128, 256), (200000, 128, 128), (0, 100, 100), (50, 513, 64)):
+    for n, k, m in ((100000, 32, 512), (50, 7, 96), (100000, 31, 64), (100000, 48, 512), (65535, 256, 256), (200000, 384, 128), (200000, 64, 512), (98303, 128, 256), (200000, 128, 128), (0, 100, 100), (50, 513, 64), (50, 100, (1 << 20) + 1)):
         assert reinc._gcn_work_bytes(n, k, m) == 0, (n, k, m)
 
 
