@@ -181,6 +181,25 @@ def test_non_finite_rows_stay_in_their_rows(ctx):
     assert torch.equal(out[keep], clean[keep])
 
 
+@pytest.mark.parametrize("n,k,m", [(130, 100, 100), (65536, 256, 256)])
+def test_infinite_operands_give_what_fp32_products_give(ctx, n, k, m):
+    """An infinite row or column of weights gives infinities of the terms' signs (so that ReLU keeps an overflowed row), and
+    NaN only where two of them cancel."""
+    import torch
+
+    assert _prepared(n, k, m)
+    g = torch.Generator(device="cuda").manual_seed(5)
+    a, w = torch.randn(n, k, generator=g, device="cuda"), torch.randn(k, m, generator=g, device="cuda")
+    a[7, 3], a[70, k - 1], w[5, 9] = float("inf"), -float("inf"), -float("inf")
+    ref = a.double() @ w.double()
+    out = ctx.gcn_transform(a, w, None, None, relu=False)
+    assert torch.equal(torch.isnan(out), torch.isnan(ref))
+    assert torch.equal(out[torch.isinf(ref)].double(), ref[torch.isinf(ref)]) and int(torch.isinf(ref).sum()) > m + n - 4
+    keep = ~torch.isnan(ref)
+    relu = ctx.gcn_transform(a, w, None, None, relu=True)
+    assert torch.equal(torch.isinf(relu[keep]), torch.isinf(torch.relu(ref)[keep])) and bool((relu[keep] >= 0).all())
+
+
 def test_shapes_that_keep_the_resident_kernels():
     from paper_2501_15348_amd import reinc
 
