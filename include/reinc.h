@@ -387,7 +387,10 @@ int reinc_get_stats(reinc_ctx *ctx, reinc_stats *out);
  * Between reinc_profile_begin and reinc_profile_end every launch of a kernel class selected in `mask`
  * (bit REINC_K_*) is bracketed by a pair of HIP events on the stream it runs on.  reinc_profile_end waits for
  * the device (SYNC) and fills launches[k] and total_ms[k] for k < REINC_K_COUNT.  At most
- * REINC_PROFILE_MAX_LAUNCHES launches are recorded per session; later ones run untimed. */
+ * REINC_PROFILE_MAX_LAUNCHES launches are recorded per session; later ones run untimed.  Work of several timesteps or
+ * classes that one launch does is launched timestep by timestep and class by class while one of its classes is selected
+ * (recurrent steps of the stacked model: REINC_K_RNN; their backward steps with the input gradient: REINC_K_ELEM,
+ * REINC_K_GEMM_ROWS). */
 #define REINC_K_AGG_FULL 0   /* wave-per-row gather of reinc_aggregate_full (forward and adjoint) */
 #define REINC_K_AGG_INC 1    /* incremental row update */
 #define REINC_K_GEMM_ROWS 2  /* row-tile GEMM (GCN update, input gradients) */

@@ -435,21 +435,41 @@ void launch_prepare_planes(const PlaneJobs &jobs, hipStream_t s);
 // as launch_gemm_rows, with the weights prepared; false: this shape is not taken
 bool launch_gemm_planes(const PlaneJob &w, const void *A, int a_bf16, int64_t n, int32_t lda, const float *row_scale, const float *bias,
                         int relu, const float *add, const float *mask, float *out, hipStream_t s);
-// as launch_rnn_fused, with the weights prepared (W1 = W_i, W2 = W_h); carry: h_carry of a GRU, c_prev of an LSTM
+// as launch_rnn_fused, with the weights prepared (W1 = W_i, W2 = W_h); carry: h_carry of a GRU, c_prev of an LSTM.  steps > 1:
+// so many timesteps, each with the one before's outputs as its state; a timestep later lies *_step floats further (no x_scale).
 bool launch_rnn_planes(const PlaneJob &w, int lstm, const float *x, const float *x_scale, int64_t n, const float *h_prev,
-                       const float *carry, const float *b_i, const float *b_h, float *h_out, float *c_out, float *saved, hipStream_t s);
-// gate gradients of one recurrent step (as launch_rnn_backward_elem) and out = dgh W_h^T (w: W_h^T prepared), with the
-// carry path of a GRU added unless carry_out takes it.  dc_out may be dc, out may be dh (without carry_out).
-bool launch_rnn_backward_planes(const PlaneJob &w, int lstm, int64_t n, int32_t H, const float *dh, const float *dc, const float *saved,
-                                const float *h_prev, const float *c_prev, const float *c_new, float *dgi, float *dgh, float *dc_out,
-                                float *carry_out, float *out, hipStream_t s);
+                       const float *carry, const float *b_i, const float *b_h, float *h_out, float *c_out, float *saved, hipStream_t s,
+                       int steps = 1, int64_t x_step = 0, int64_t state_step = 0, int64_t saved_step = 0);
+// Gate gradients of `steps` recurrent steps, the latest first, with their products with W_h^T (the gradient w.r.t. the state
+// before each step) and, where dz is given, W_i^T.  Pointers are those of the latest timestep; a timestep earlier lies *_step
+// floats before.  wh, wi: the transposed weights prepared (not read where rnn_backward_exact).
+struct RnnBackward {
+    int64_t n;
+    int32_t H, d;          // hidden units, inputs of the cell
+    int32_t steps;
+    int to_first;          // the earliest of them is the window's first: no state before it, no gradient of it
+    const float *W_h, *W_i;
+    const float *dh, *dc;  // gradient w.r.t. the latest state (LSTM: and c, null = 0)
+    const float *saved, *h_prev, *c_prev, *c_new;  // GRU: h_prev; LSTM: c_prev, c_new
+    float *dg;             // [n, 4 H]: LSTM di, df, dg, do; GRU dr, dz, dn, dn .* r
+    const float *mask;     // [n, d]: dz is zero where it is not positive
+    float *dz;             // [n, d] gradient w.r.t. the cell's input, or null
+    int64_t saved_step, state_step, dg_step, mask_step, dz_step;
+    float *dc_out;         // LSTM: gradient w.r.t. the c before the earliest step (may be dc)
+    float *carry_out;      // GRU, one step: receives dh .* z, which is then left out of `out`; or null
+    float *out;            // gradient w.r.t. the state before the earliest step (may be dh)
+};
+bool rnn_backward_planes_shape(int32_t H);
+bool rnn_backward_exact(int lstm, int32_t H);
+bool launch_rnn_backward_planes(const PlaneJob *wh, const PlaneJob *wi, int lstm, const RnnBackward &b, hipStream_t s);
 uint64_t reduce_partial_bytes(int64_t n, int32_t K, int32_t M);
 // partial[chunk] (+)= (row_scale .* A)^T G over the chunk's rows, with the column sums of G in row K; `accumulate`
 // adds to what the slabs hold.  The slab geometry is that of n_geom >= n rows, so that calls over different row
 // counts can add into one set of slabs (sized by reduce_partial_bytes(n_geom, K, M)).  launch_reduce_partials
-// (with the same n_geom) then does dW[K,M] += sum of slabs, db[M] += sum of rows K.
+// (with the same n_geom) then does dW[K,M] += sum of slabs, db[M] += sum of rows K.  Column c of G lies at c, from
+// `gap_at` on `gap` columns further.
 void launch_gemm_reduce(const float *A, int32_t lda, const float *row_scale, const float *G, int32_t ldg, int64_t n,
-                        int64_t n_geom, int32_t K, int32_t M, float *partial, int accumulate, hipStream_t s);
+                        int64_t n_geom, int32_t K, int32_t M, float *partial, int accumulate, int32_t gap_at, int32_t gap, hipStream_t s);
 void launch_reduce_partials(const float *partial, int64_t n, int32_t K, int32_t M, float *dW, float *db, hipStream_t s);
 void launch_rnn_backward_elem(int lstm, int64_t n, int32_t H, const float *dh, const float *dc, const float *saved,
                               const float *h_prev, const float *c_prev, const float *c_new, float *dgi, float *dgh,

@@ -1306,6 +1306,7 @@ struct ReduceArgs {
     float *partial;  // [chunks, K+1, M]
     int chunks;
     int accumulate;  // add to the partial slabs instead of overwriting them (later timesteps of a window)
+    int gap_at, gap; // column c of G lies at c, from gap_at on `gap` columns further
 };
 
 // One trip of a wave on the bf16 matrix cores: the lane's eight values per operand are eight rows of the trip
@@ -1376,6 +1377,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))
     float bsum[2] = {0.0f, 0.0f};
     const bool fa0 = f0 + i < g.K, fa1 = f0 + 32 + i < g.K;
     const bool cb0 = c0 + i < g.M, cb1 = c0 + 32 + i < g.M;
+    const int gc0 = i + (c0 + i >= g.gap_at ? g.gap : 0), gc1 = 32 + i + (c0 + 32 + i >= g.gap_at ? g.gap : 0);  // the lane's columns of G behind c0
     // Wave w takes row pairs w, w+4, ... of the chunk, kRU pairs (64 rows of the block) per trip.  Full trips
     // over full 64x64 slabs run without a branch and double-buffered: the loads of the next trip are issued
     // before the matrix instructions of the current one, and while a next trip exists they are unconditional
@@ -1395,7 +1397,8 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))
     if constexpr (SPLIT && WIDE) {
         // (chunks of fewer than five trips take the per-wave path below: the pipeline here starts with two trips
         // in flight and its loop runs at least once)
-        shared_split = wx == 2 && (slab % slabs_x + 1) * 128 <= g.K && (slab / slabs_x + 1) * 128 <= g.M && r_end - r_begin >= 5 * 16;
+        shared_split = wx == 2 && (slab % slabs_x + 1) * 128 <= g.K && (slab / slabs_x + 1) * 128 <= g.M && r_end - r_begin >= 5 * 16 &&
+                       (g.gap_at % 64 == 0 || g.gap_at >= g.M);  // (a piece of 64 columns has no gap inside)
         if (shared_split) {
             // [buffer][piece][plane][32-column half][lane]: a lane's record sits at its lane index, so that the lanes
             // of a 128-bit LDS access cover consecutive 16-byte records (records two apart cost every access twice)
@@ -1410,7 +1413,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))
             // iteration wait for all loads but the newest group, which left one trip in flight instead of two.
             // Addresses: a wave-uniform base (scalar registers, advanced once per trip) plus one fixed 32-bit
             // lane offset per row pair; the second 32 columns ride on the instruction's offset field.
-            const float *pp = (a_piece ? g.A : g.G) + base * ld + pcol0;
+            const float *pp = (a_piece ? g.A : g.G) + base * ld + pcol0 + (!a_piece && pcol0 >= g.gap_at ? g.gap : 0);
             const float *sp = HAS_RS ? g.row_scale + base : nullptr;  // (every wave loads the scales: equal load counts)
             unsigned voff[kRU], soff[kRU];
 #pragma unroll
@@ -1541,7 +1544,8 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))
         const float *ap = g.A + (base + wu) * g.lda + f0;
         const float *gp = g.G + (base + wu) * g.ldg + c0;
         const float *sp = HAS_RS ? g.row_scale + base + wu : nullptr;
-        const unsigned aoff = unsigned(kk) * unsigned(g.lda) + i, goff = unsigned(kk) * unsigned(g.ldg) + i;
+        const unsigned aoff = unsigned(kk) * unsigned(g.lda) + i, goff0 = unsigned(kk) * unsigned(g.ldg) + gc0,
+                       goff1 = unsigned(kk) * unsigned(g.ldg) + gc1;
         // a trip's operands: [0] [1] = the two 32-column halves of the A rows, [2] [3] = of the G rows, [4] = row scale
         auto load = [&](float(&t)[5][kRU]) __attribute__((always_inline)) {
 #pragma unroll
@@ -1549,8 +1553,8 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))
                 const float *au = ap + int64_t(rstep * u) * g.lda, *gu = gp + int64_t(rstep * u) * g.ldg;
                 t[0][u] = au[aoff];
                 t[1][u] = au[aoff + 32];
-                t[2][u] = gu[goff];
-                t[3][u] = gu[goff + 32];
+                t[2][u] = gu[goff0];
+                t[3][u] = gu[goff1];
                 t[4][u] = HAS_RS ? sp[rstep * u + kk] : 1.0f;
             }
             ap += int64_t(trip) * g.lda;
@@ -1625,11 +1629,11 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))
             if (r < r_end) {
                 const float sc = HAS_RS ? g.row_scale[r] : 1.0f;
                 const float *ap = g.A + r * g.lda + f0 + i;
-                const float *gp = g.G + r * g.ldg + c0 + i;
+                const float *gp = g.G + r * g.ldg + c0;
                 if (fa0) a0[u] = ap[0] * sc;
                 if (fa1) a1[u] = ap[32] * sc;
-                if (cb0) b0[u] = gp[0];
-                if (cb1) b1[u] = gp[32];
+                if (cb0) b0[u] = gp[gc0];
+                if (cb1) b1[u] = gp[gc1];
             }
         }
         if (SPLIT) {
@@ -2041,7 +2045,7 @@ uint64_t reduce_partial_bytes(int64_t n, int32_t K, int32_t M)
 }
 
 void launch_gemm_reduce(const float *A, int32_t lda, const float *row_scale, const float *G, int32_t ldg, int64_t n,
-                        int64_t n_geom, int32_t K, int32_t M, float *partial, int accumulate, hipStream_t s)
+                        int64_t n_geom, int32_t K, int32_t M, float *partial, int accumulate, int32_t gap_at, int32_t gap, hipStream_t s)
 {
     if (n <= 0 || n_geom < n) return;
     // the chunk geometry (how many slabs, how many rows each) belongs to n_geom rows: calls with fewer rows fill
@@ -2049,7 +2053,7 @@ void launch_gemm_reduce(const float *A, int32_t lda, const float *row_scale, con
     const int chunks = reduce_chunks(n_geom, K, M);
     int64_t rpc = (n_geom + chunks - 1) / chunks;
     rpc = (rpc + 63) & ~int64_t(63);  // whole 64-row trips; no row pair straddles two chunks
-    ReduceArgs g{A, lda, row_scale, G, ldg, n, K, M, rpc, partial, chunks, accumulate};
+    ReduceArgs g{A, lda, row_scale, G, ldg, n, K, M, rpc, partial, chunks, accumulate, gap_at, gap};
     const int slabs = reduce_block_slabs(K, M);
     const unsigned blocks = unsigned(slabs) * unsigned((chunks + 7) / 8) * 8u;
     const bool split = dense_split_enabled(), wide = reduce_wide(K, M);

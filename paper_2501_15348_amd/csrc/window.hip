@@ -2,6 +2,7 @@
 // consecutive snapshots is one training sample with back-propagation through time; Section 3.3: a global
 // cache for the aggregates of the input features, a local cache for per-layer intermediates).
 #include <algorithm>
+#include <climits>
 #include <initializer_list>
 #include <vector>
 
@@ -63,10 +64,13 @@ struct Planes {
 
 // out[n,M] = epilogue((row_scale .* A)[n,K] * B[K,M]) with B = W or W^T, prepared (w) or not
 void product(reinc_ctx *ctx, hipStream_t st, const PlaneJob *w, const float *A, int64_t n, int K, int M, const float *row_scale,
-             const float *W, int wT, int ldw, const float *bias, int relu, const float *add, const float *mask, float *out)
+             const float *W, int wT, int ldw, const float *bias, int relu, const float *add, const float *mask, float *out, int lda = 0)
 {
     ProfScope prof(ctx, REINC_K_GEMM_ROWS, st);
-    if (w && planes_pay_backward(n, K, M) && launch_gemm_planes(*w, A, 0, n, K, row_scale, bias, relu, add, mask, out, st)) return;
+    const bool apart = lda > K;  // (rows that lie apart are for the plane kernel)
+    if (w && (apart || planes_pay_backward(n, K, M)) &&
+        launch_gemm_planes(*w, A, 0, n, apart ? lda : K, row_scale, bias, relu, add, mask, out, st))
+        return;
     launch_gemm_rows(A, 0, n, K, M, row_scale, W, wT, ldw, bias, relu, add, mask, out, st);
 }
 
@@ -80,16 +84,12 @@ void rnn_step(reinc_ctx *ctx, hipStream_t st, const PlaneJob *w, int lstm, const
     launch_rnn_fused(lstm, x, x_scale, n, d_in, H, h_prev, h_carry, c_prev, W_i, W_h, b_i, b_h, h_out, c_out, saved, st);
 }
 
-// gate gradients and the gradient w.r.t. the previous state in one launch; false: not for this shape
-bool rnn_backward_step(reinc_ctx *ctx, hipStream_t st, const PlaneJob *whT, int lstm, int64_t n, int H, const float *dh, const float *dc,
-                       const float *saved, const float *h_prev, const float *c_prev, const float *c_new, float *dgi, float *dgh,
-                       float *dc_out, float *carry_out, float *out)
+// recurrent steps back in time with their products; see launch_rnn_backward_planes
+int rnn_backward_steps(reinc_ctx *ctx, hipStream_t st, const PlaneJob *wh, const PlaneJob *wi, int lstm, const RnnBackward &b)
 {
-    if (!whT) return false;
     ProfScope prof(ctx, REINC_K_ELEM, st);
-    if (launch_rnn_backward_planes(*whT, lstm, n, H, dh, dc, saved, h_prev, c_prev, c_new, dgi, dgh, dc_out, carry_out, out, st)) return true;
-    prof.drop();
-    return false;
+    if (!launch_rnn_backward_planes(wh, wi, lstm, b, st)) return ctx->fail(REINC_E_HIP, "the recurrent backward kernel cannot be launched");
+    return REINC_OK;
 }
 
 struct Params {
@@ -725,6 +725,15 @@ int reinc_forward_window(reinc_ctx *ctx, int32_t t0, int32_t L, const float *par
                                    return REINC_OK;
                                }));
         }
+        // all timesteps of the batch in one launch; one by one while recurrent steps are being timed
+        if (const PlaneJob *w = planes.get(plane_rnn); w && hi > lo && !(ctx->prof_mask & (1u << REINC_K_RNN))) {
+            LocalStep &st = ctx->local[lo];
+            const LocalStep *pv = lo ? &ctx->local[lo - 1] : nullptr;
+            const float *hp = pv ? (const float *)pv->h : nof;
+            if (launch_rnn_planes(*w, lstm, st.H[Lg], nof, nt, hp, lstm && pv ? pv->c : hp, p.b_i, p.b_h, st.h, st.c, st.saved, s, hi - lo + 1,
+                                  int64_t(slice_floats(nt, c.dims[Lg])), int64_t(slice_floats(nt, H)), int64_t(slice_floats(nt, 4 * H))))
+                continue;
+        }
         for (int32_t i = lo; i <= hi; ++i) {
             LocalStep &st = ctx->local[i];
             const LocalStep *pv = i ? &ctx->local[i - 1] : nullptr;
@@ -785,7 +794,7 @@ int reinc_backward_window(reinc_ctx *ctx, int32_t t0, int32_t L, const float *pa
     auto batch_bytes = [&](int B) {
         const uint64_t rows = uint64_t(B) * uint64_t(n);
         uint64_t b = align256(uint64_t(B) * uint64_t(scale_rows) * 4);
-        b += align256(rows * KH * 4) * (lstm ? 1 : 2) + 3 * align256(rows * maxd * 4);
+        b += align256(rows * KH * 4) * (lstm ? 1 : 2) + 3 * align256(rows * maxd * 4);  // (a GRU's 4 H floats once, or 3 H twice)
         b += align256(reduce_partial_bytes(int64_t(rows), c.dims[Lg], KH)) + align256(reduce_partial_bytes(int64_t(rows), H, KH));
         for (int l = 1; l <= Lg; ++l) b += align256(reduce_partial_bytes(int64_t(rows), c.dims[l - 1], c.dims[l]));
         return b + align256(column_sums_bytes(maxd));
@@ -810,8 +819,13 @@ int reinc_backward_window(reinc_ctx *ctx, int32_t t0, int32_t L, const float *pa
     }
     const int64_t rowsB = int64_t(B) * n;
     const int64_t rowsT = int64_t(B) * nt;  // rows of a batch of timesteps in the top quantities
-    float *dgi = f32(uint64_t(rowsB) * KH);
-    float *dgh = lstm ? dgi : f32(uint64_t(rowsB) * KH);
+    // all steps of a batch back in time in one launch, which keeps a GRU's gate gradients as one array of 4 H columns
+    const bool chain = rnn_backward_planes_shape(H) && (rnn_backward_exact(lstm, H) || (plane_whT >= 0 && plane_wiT >= 0));
+    // ... unless one of the kinds of work that this launch does is being timed: then they are launched apart
+    const bool apart = chain && plane_wiT >= 0 && (ctx->prof_mask & (1u << REINC_K_ELEM | 1u << REINC_K_GEMM_ROWS));
+    const int ldg = chain ? 4 * H : KH;
+    float *dgi = f32(uint64_t(rowsB) * ldg);
+    float *dgh = lstm || chain ? dgi : f32(uint64_t(rowsB) * ldg);
     float *dz = f32(uint64_t(rowsB) * maxd), *dz2 = f32(uint64_t(rowsB) * maxd), *dagg = f32(uint64_t(rowsB) * maxd);
     // one set of partial slabs per weight matrix: they collect all batches and are reduced once at the end
     float *part_wi = static_cast<float *>(ctx->scratch(reduce_partial_bytes(rowsT, c.dims[Lg], KH)));
@@ -843,22 +857,45 @@ int reinc_backward_window(reinc_ctx *ctx, int32_t t0, int32_t L, const float *pa
     // The partial slabs of a weight always belong to the same number of rows (B timesteps): a shorter last batch
     // uses the chunk geometry of a full one, so that every batch adds into the same slabs.
     auto reduce = [&](const float *A, int lda, const float *rs, const float *G, int ldg, int64_t rows, int64_t rows_geom, int K, int M,
-                      float *part, int accumulate) { gemm_reduce(ctx, s, A, lda, rs, G, ldg, rows, rows_geom, K, M, part, accumulate); };
+                      float *part, int accumulate, int gap_at = INT_MAX) {
+        gemm_reduce(ctx, s, A, lda, rs, G, ldg, rows, rows_geom, K, M, part, accumulate, gap_at, H);
+    };
     bool first_batch = true;
     for (int32_t hi = L - 1; hi >= 0;) {
         const int32_t lo = std::max(0, hi - B + 1);
         const int nb = hi - lo + 1;
+        const int dl = c.dims[Lg];
         // the recurrent chain of the batch, last timestep first
-        for (int32_t i = hi; i >= lo; --i) {
+        if (chain) {
+            const LocalStep &st = ctx->local[hi], &pv = ctx->local[std::max(hi - 1, 0)];
+            RnnBackward b{};
+            b.n = nt, b.H = H, b.d = dl, b.steps = nb, b.to_first = lo == 0;
+            b.W_h = p.W_h, b.W_i = p.W_i;
+            b.dh = dh, b.dc = dc_in, b.saved = st.saved, b.h_prev = pv.h, b.c_prev = pv.c, b.c_new = st.c;
+            b.dg = dgi + int64_t(nb - 1) * nt * ldg;
+            b.mask = st.H[Lg], b.dz = dz + int64_t(nb - 1) * nt * dl;
+            b.saved_step = int64_t(slice_floats(nt, 4 * H)), b.state_step = int64_t(slice_floats(nt, H));
+            b.dg_step = nt * ldg, b.mask_step = int64_t(slice_floats(nt, dl)), b.dz_step = nt * dl;
+            b.dc_out = dc, b.out = dh;
+            if (apart) {
+                b.dz = nullptr, b.steps = 1;
+                for (int32_t i = hi; i >= lo; --i) {
+                    const LocalStep &si = ctx->local[i], &before = ctx->local[std::max(i - 1, 0)];
+                    b.to_first = i == 0, b.dc = dc_in;
+                    b.saved = si.saved, b.h_prev = before.h, b.c_prev = before.c, b.c_new = si.c;
+                    b.dg = dgi + int64_t(i - lo) * nt * ldg;
+                    REINC_TRY(rnn_backward_steps(ctx, s, planes.get(plane_whT), nullptr, lstm, b));
+                    if (lstm) dc_in = dc;
+                }
+            } else {
+                REINC_TRY(rnn_backward_steps(ctx, s, planes.get(plane_whT), planes.get(plane_wiT), lstm, b));
+                if (lstm) dc_in = dc;
+            }
+        }
+        for (int32_t i = hi; i >= lo && !chain; --i) {
             const LocalStep &st = ctx->local[i];
             const LocalStep *pv = i ? &ctx->local[i - 1] : nullptr;
             float *dgi_i = dgi + int64_t(i - lo) * nt * KH, *dgh_i = dgh + int64_t(i - lo) * nt * KH;
-            // (the step's own input gradients are overwritten by the previous step's: dh and, once there is one, dc)
-            if (i > 0 && rnn_backward_step(ctx, s, planes.get(plane_whT), lstm, nt, H, dh, dc_in, st.saved, pv->h, pv->c, st.c, dgi_i, dgh_i,
-                                           dc, nullptr, dh)) {
-                if (lstm) dc_in = dc;
-                continue;
-            }
             rnn_backward_elem(ctx, s, lstm, nt, H, (const float *)dh, dc_in, (const float *)st.saved,
                               pv ? (const float *)pv->h : nof, pv ? (const float *)pv->c : nof, (const float *)st.c, dgi_i, dgh_i,
                               dh2, dc2);
@@ -876,7 +913,6 @@ int reinc_backward_window(reinc_ctx *ctx, int32_t t0, int32_t L, const float *pa
         }
         const bool has_q = q[lo] != nullptr;
         const int acc0 = first_batch ? 0 : 1;
-        const int dl = c.dims[Lg];
         // recurrent weights: x_t = H^{Lg}_t against the x-side gate gradients, h_{t-1} against the h-side ones
         for (int32_t i = lo; i <= hi; ++i) {
             Ap[i] = ctx->local[i].H[Lg];
@@ -884,18 +920,19 @@ int reinc_backward_window(reinc_ctx *ctx, int32_t t0, int32_t L, const float *pa
         }
         int calls = 0;
         REINC_TRY(for_runs(lo, hi, nt, {Strip{Ap.data(), dl}}, [&](int i0, int len) {
-            reduce(Ap[i0], dl, nof, dgi + int64_t(i0 - lo) * nt * KH, KH, nt * len, rowsT, dl, KH, part_wi, acc0 | (calls++ > 0));
+            reduce(Ap[i0], dl, nof, dgi + int64_t(i0 - lo) * nt * ldg, ldg, nt * len, rowsT, dl, KH, part_wi, acc0 | (calls++ > 0));
             return REINC_OK;
         }));
         calls = 0;
         REINC_TRY(for_runs(lo, hi, nt, {Strip{Mp.data(), H}}, [&](int i0, int len) {
-            reduce(Mp[i0], H, nof, dgh + int64_t(i0 - lo) * nt * KH, KH, nt * len, rowsT, H, KH, part_wh, acc0 | (calls++ > 0));
+            reduce(Mp[i0], H, nof, dgh + int64_t(i0 - lo) * nt * ldg, ldg, nt * len, rowsT, H, KH, part_wh, acc0 | (calls++ > 0),
+                   chain && !lstm ? 2 * H : INT_MAX);
             return REINC_OK;
         }));
         // gradient w.r.t. the last GCN layer's pre-activation, all timesteps of the batch
-        REINC_TRY(for_runs(lo, hi, nt, {Strip{Ap.data(), dl}}, [&](int i0, int len) {
-            product(ctx, s, planes.get(plane_wiT), dgi + int64_t(i0 - lo) * nt * KH, nt * len, KH, dl, nof, p.W_i, 1, KH, nof, 0, nof,
-                    Ap[i0], dz + int64_t(i0 - lo) * nt * dl);
+        if (!chain || apart) REINC_TRY(for_runs(lo, hi, nt, {Strip{Ap.data(), dl}}, [&](int i0, int len) {
+            product(ctx, s, planes.get(plane_wiT), dgi + int64_t(i0 - lo) * nt * ldg, nt * len, KH, dl, nof, p.W_i, 1, KH, nof, 0, nof,
+                    Ap[i0], dz + int64_t(i0 - lo) * nt * dl, ldg);
             return REINC_OK;
         }));
         for (int l = Lg; l >= 1; --l) {
@@ -1108,8 +1145,10 @@ int reinc_backward_window_integrated(reinc_ctx *ctx, int32_t t0, int32_t L, cons
         return ctx->fail(REINC_E_NOMEM, "arena exhausted: no room for the backward scratch buffers");
     }
     const int64_t rowsB = int64_t(B) * n;
-    float *dgi = f32(uint64_t(rowsB) * KH);
-    float *dgh = lstm ? dgi : f32(uint64_t(rowsB) * KH);
+    const bool fused = rnn_backward_planes_shape(H) && (rnn_backward_exact(lstm, H) || plane_whT >= 0);  // (see reinc_backward_window)
+    const int ldg = fused ? 4 * H : KH, gap_at = fused && !lstm ? 2 * H : INT_MAX;
+    float *dgi = f32(uint64_t(rowsB) * ldg);
+    float *dgh = lstm || fused ? dgi : f32(uint64_t(rowsB) * ldg);
     float *part_wi = static_cast<float *>(ctx->scratch(reduce_partial_bytes(rowsB, d0, KH)));
     float *part_wh = static_cast<float *>(ctx->scratch(reduce_partial_bytes(rowsB, H, KH)));
     if (!dgi || !dgh || !part_wi || !part_wh) {
@@ -1144,10 +1183,15 @@ int reinc_backward_window_integrated(reinc_ctx *ctx, int32_t t0, int32_t L, cons
             const LocalStep &st = ctx->local[i];
             const LocalStep *pv = i ? &ctx->local[i - 1] : nullptr;
             const int64_t ni = rows_of[size_t(i)];
-            float *dgi_i = dgi + int64_t(i - lo) * n * KH, *dgh_i = dgh + int64_t(i - lo) * n * KH;
-            const bool fused = i > 0 && rnn_backward_step(ctx, s, planes.get(plane_whT), lstm, ni, H, dh, dc_in, st.saved, pv->h, pv->c, st.c,
-                                                          dgi_i, dgh_i, dc2, lstm ? nullptr : dh2, dah);
-            if (!fused)
+            float *dgi_i = dgi + int64_t(i - lo) * n * ldg, *dgh_i = dgh + int64_t(i - lo) * n * ldg;
+            if (fused) {
+                RnnBackward b{};
+                b.n = ni, b.H = H, b.steps = 1, b.to_first = i == 0;
+                b.W_h = W_h;
+                b.dh = dh, b.dc = dc_in, b.saved = st.saved, b.h_prev = pv ? pv->h : st.h, b.c_prev = pv ? pv->c : st.c, b.c_new = st.c;
+                b.dg = dgi_i, b.dc_out = dc2, b.carry_out = lstm ? nullptr : dh2, b.out = dah;
+                REINC_TRY(rnn_backward_steps(ctx, s, planes.get(plane_whT), nullptr, lstm, b));
+            } else
                 rnn_backward_elem(ctx, s, lstm, ni, H, (const float *)dh, dc_in, (const float *)st.saved,
                                   pv ? (const float *)pv->h : nof, pv ? (const float *)pv->c : nof, (const float *)st.c, dgi_i, dgh_i,
                                   dh2, dc2);
@@ -1182,24 +1226,24 @@ int reinc_backward_window_integrated(reinc_ctx *ctx, int32_t t0, int32_t L, cons
             // every timestep has its own row count: one reduction each, over the rows that exist
             for (int32_t i = lo; i <= hi; ++i, ++calls) {
                 const int64_t ni = rows_of[size_t(i)];
-                gemm_reduce(ctx, s, s1[i], d0, q[i], (const float *)(dgi + int64_t(i - lo) * n * KH), KH, ni, rowsB, d0, KH, part_wi,
-                            acc0 | (calls > 0));
-                gemm_reduce(ctx, s, ah[i], H, nof, (const float *)(dgh + int64_t(i - lo) * n * KH), KH, ni, rowsB, H, KH, part_wh,
-                            acc0 | (calls > 0));
+                gemm_reduce(ctx, s, s1[i], d0, q[i], (const float *)(dgi + int64_t(i - lo) * n * ldg), ldg, ni, rowsB, d0, KH, part_wi,
+                            acc0 | (calls > 0), INT_MAX, H);
+                gemm_reduce(ctx, s, ah[i], H, nof, (const float *)(dgh + int64_t(i - lo) * n * ldg), ldg, ni, rowsB, H, KH, part_wh,
+                            acc0 | (calls > 0), gap_at, H);
             }
             first_batch = false;
             hi = lo - 1;
             continue;
         }
         REINC_TRY(for_runs(lo, hi, n, {Strip{s1.data(), d0}, Strip{has_q ? q.data() : nullptr, 1}}, [&](int i0, int len) {
-            gemm_reduce(ctx, s, s1[i0], d0, q[i0], (const float *)(dgi + int64_t(i0 - lo) * n * KH), KH, n * len, rowsB, d0, KH,
-                        part_wi, acc0 | (calls++ > 0));
+            gemm_reduce(ctx, s, s1[i0], d0, q[i0], (const float *)(dgi + int64_t(i0 - lo) * n * ldg), ldg, n * len, rowsB, d0, KH,
+                        part_wi, acc0 | (calls++ > 0), INT_MAX, H);
             return REINC_OK;
         }));
         calls = 0;
         REINC_TRY(for_runs(lo, hi, n, {Strip{ah.data(), H}}, [&](int i0, int len) {
-            gemm_reduce(ctx, s, ah[i0], H, nof, (const float *)(dgh + int64_t(i0 - lo) * n * KH), KH, n * len, rowsB, H, KH, part_wh,
-                        acc0 | (calls++ > 0));
+            gemm_reduce(ctx, s, ah[i0], H, nof, (const float *)(dgh + int64_t(i0 - lo) * n * ldg), ldg, n * len, rowsB, H, KH, part_wh,
+                        acc0 | (calls++ > 0), gap_at, H);
             return REINC_OK;
         }));
         first_batch = false;

@@ -481,3 +481,48 @@ def test_profile_counts_launches_of_the_backward_recurrence_once(hidden, product
     seen = {k: v[0] for k, v in ctx.profile_end().items()}
     assert seen["elem"] == 3 and seen["gemm_rows"] == products + 1, seen  # (and W_i^T's, all timesteps at once)
     ctx.close()
+
+
+# The timesteps of a window in one launch per direction, the backward one with the input's gradient: both sides of each block
+# shape's hidden width, parts of a row that are no whole k-steps, more and fewer column tiles of the input than waves, the
+# fp32 instructions (GRU 16, LSTM 8), ragged rows; few rows (no room for the forward weights) and more.
+@pytest.mark.parametrize("rnn", ["gru", "lstm"])
+@pytest.mark.parametrize("n,hidden,top", [(33, 8, 24), (321, 16, 16), (70, 16, 72), (65, 24, 33), (321, 32, 96), (645, 64, 130), (31, 64, 32),
+                                          (129, 40, 200), (70, 96, 64), (833, 128, 160), (96, 128, 31), (65, 104, 48)])
+def test_steps_of_a_window_in_one_launch(rnn, n, hidden, top):
+    import torch
+
+    from helpers import GRAD_RTOL_FP32, assert_gradients_close, oracle_feats, oracle_graphs
+    from paper_2501_15348_amd import reinc, synth
+
+    length = 4
+    wl = synth.WORKLOADS["c3"].scaled(n, length, dims=(16, top), hidden=hidden, rnn=rnn, mean_degree=4.0)
+    seq = synth.make_sequence(wl)
+    ctx = reinc.Context.for_workload(wl, arena_bytes=1 << 27)
+    ctx.load_sequence(seq)
+    ctx.build_deltas(-1)
+    flat, target = synth.make_params(wl, bias_scale=0.2), synth.make_target(wl)
+    params, tgt = torch.from_numpy(flat).cuda(), torch.from_numpy(target).cuda()
+
+    def run(timed):
+        out = [torch.zeros(1, device="cuda"), torch.full((n, hidden), 7.0, device="cuda"), torch.empty_like(params)]
+        if timed:  # (timestep by timestep)
+            ctx.profile_begin(["rnn", "elem", "gemm_rows"])
+        ctx.forward_window(0, length, params, tgt, out[0], out[1])
+        ctx.backward_window(0, length, params, tgt, out[2])
+        if timed:
+            ctx.profile_end()
+        torch.cuda.synchronize()
+        return out
+
+    one, apart = run(False), run(True)
+    assert torch.equal(one[0], apart[0]) and torch.equal(one[1], apart[1])  # (the same arithmetic)
+    assert_close(one[2].cpu().numpy(), apart[2].cpu().numpy(), RTOL_FP32, "gradients, together and apart")
+    p = synth.split_params(wl, flat.astype(np.float64))
+    graphs, feats = oracle_graphs(seq), [oracle_feats(seq, t) for t in range(length)]
+    _, ref_h, saved = oracle.forward_window(graphs, feats, p, 1, wl.agg, wl.self_loop, rnn, target, keep=True)
+    assert_close(one[1].cpu().numpy(), ref_h, RTOL_FP32, "h_last")
+    assert_gradients_close(synth.split_params(wl, one[2].cpu().numpy()), saved,
+                           lambda sv: oracle.backward_window(graphs, sv, ref_h, p, 1, wl.agg, wl.self_loop, rnn, target),
+                           [name for name, _ in synth.param_shapes(wl)], GRAD_RTOL_FP32)
+    ctx.close()
