@@ -27,7 +27,6 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0  # MI355X HBM3E
-LONG_ROW = 64  # rows with more entries than this are aggregated by the block-per-row kernel
 MAX_BATCH = 8  # timesteps of a window that the driver hands to one launch
 DEFAULT_WORKLOAD = "c4"  # the largest configuration that fits one GPU
 
@@ -212,26 +211,17 @@ def main():
                     "frac": 0.0, "traffic": None, "launches": 0,
                     "note": "no incremental step in the timed region: every step is above the fallback threshold"}
 
-    # ---- second block: aggregate_rows_grouped, the from-scratch gather (layer-1 steps that are not incremental,
-    # and every layer above the first, forward and adjoint).  It takes every row of at most LONG_ROW entries (longer
-    # rows go to a block-per-row kernel that is not part of this figure): algorithmic bytes of exactly the rows it
-    # handles / its measured launch time
+    # ---- second block: aggregate_rows, the from-scratch gather (layer-1 steps that are not incremental, and every layer
+    # above the first, forward and adjoint): algorithmic bytes / its measured launch time
     launches, total_ms = prof["agg_full"]
     layers = len(wl.dims) - 1
-    fwd_short, adj_short = [], []  # per snapshot: (edges, rows) handled by the grouped kernel, CSR and CSC side
-    for t in range(T):
-        for transpose, acc in ((False, fwd_short), (True, adj_short)):
-            ptr, _ = ctx.get_snapshot_csr(t, transpose)
-            deg = np.diff(ptr)
-            short = deg <= LONG_ROW
-            acc.append((float(deg[short].sum()), float(short.sum())))
+    edges = [float(ctx.get_snapshot_csr(t)[0][-1]) for t in range(T)]
 
-    def short_bytes(t, side, d, el):
-        e_s, n_s = (fwd_short if side == "fwd" else adj_short)[t]
-        return e_s * (4 + d * el) + n * 16 + n_s * d * 4
+    def gather_bytes(t, d, el):
+        return edges[t] * (4 + d * el) + n * 16 + n * d * 4
 
     total_bytes, count = 0.0, 0.0
-    mean_l1 = float(np.mean([short_bytes(t, "fwd", d0, elem) for t in range(T)]))
+    mean_l1 = float(np.mean([gather_bytes(t, d0, elem) for t in range(T)]))
     total_bytes += full_steps * mean_l1
     count += full_steps
     batches = -(-L // MAX_BATCH)  # above layer 1 one launch aggregates up to MAX_BATCH snapshots of a window
@@ -241,15 +231,15 @@ def main():
             # a layer that narrows its input applies its linear map first and gathers rows of its own width
             width = wl.dims[l] if wl.dims[l] < wl.dims[l - 1] else wl.dims[l - 1]
             for t in range(t0_, t0_ + L):
-                total_bytes += short_bytes(t, "fwd", width, 4) + short_bytes(t, "adj", width, 4)
+                total_bytes += 2 * gather_bytes(t, width, 4)
     # (a launch covers one snapshot at layer 1 and up to MAX_BATCH snapshots above it -- fewer where the arena leaves
     # less scratch -- so the bytes of all launches are set against their total duration)
     bytes_per_launch = total_bytes * args.steps / max(launches, 1)
     avg_ms = total_ms / max(launches, 1)
     full_achieved = bytes_per_launch / (avg_ms * 1e-3) / 1e9 if launches else 0.0
-    full_traffic = measured_traffic(wl.name, "aggregate_rows_grouped")
+    full_traffic = measured_traffic(wl.name, "aggregate_rows<")
     roofline_full = {
-        "bound": "hbm", "kernel": "aggregate_rows_grouped (Eq. 1 and its adjoint, rows of at most 64 entries)",
+        "bound": "hbm", "kernel": "aggregate_rows (Eq. 1 and its adjoint)",
         "achieved": round(full_achieved, 1), "peak": HBM_PEAK_GBS,
         "unit": "GB/s", "frac": round(full_achieved / HBM_PEAK_GBS, 4), "traffic": full_traffic,
         "traffic_frac": round(full_traffic / (avg_ms * 1e-3) / 1e9 / HBM_PEAK_GBS, 4) if full_traffic and launches else None,

@@ -391,7 +391,7 @@ int reinc_get_stats(reinc_ctx *ctx, reinc_stats *out);
  * classes that one launch does is launched timestep by timestep and class by class while one of its classes is selected
  * (recurrent steps of the stacked model: REINC_K_RNN; their backward steps with the input gradient: REINC_K_ELEM,
  * REINC_K_GEMM_ROWS). */
-#define REINC_K_AGG_FULL 0   /* wave-per-row gather of reinc_aggregate_full (forward and adjoint) */
+#define REINC_K_AGG_FULL 0   /* gather of reinc_aggregate_full (forward and adjoint) */
 #define REINC_K_AGG_INC 1    /* incremental row update */
 #define REINC_K_GEMM_ROWS 2  /* row-tile GEMM (GCN update, input gradients) */
 #define REINC_K_RNN 3        /* fused recurrent step */

@@ -356,14 +356,12 @@ bool agg_width_supported(int32_t d, int bf16);
 // in_scale / out_scale may be null (factor 1); then + bias and relu (AggItem); mask [n,d] (may be null) zeroes the
 // output where mask <= 0.
 // One launch serves a batch of up to kMaxAggBatch snapshots (blockIdx.y picks the item): the layers above the
-// first aggregate every timestep of a window in one go.  launch_aggregate_batch takes every row of at most kLongRow
-// entries (all rows of an item with n_long == 0); launch_aggregate_long_batch takes the listed long rows with one
-// block each.
+// first aggregate every timestep of a window in one go.  The listed long rows get a block each, every other row (all
+// rows of an item with n_long == 0) a group of lanes.
 void launch_aggregate_batch(const AggBatch &batch, int bf16, int32_t d, int64_t n, int self_loop, hipStream_t s,
                             hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr);
-void launch_aggregate_long_batch(const AggBatch &batch, int bf16, int32_t d, int self_loop, hipStream_t s);
-// both, with the main kernel timed as REINC_K_AGG_FULL; n_rows >= 0: only rows [0, n_rows) of the short-row kernel
-// (listed long rows beyond it are still computed)
+// the same, timed as REINC_K_AGG_FULL; n_rows >= 0: only rows [0, n_rows) of those that are not listed (listed long rows
+// beyond it are still computed)
 void aggregate_full_batch(reinc_ctx *ctx, const AggBatch &batch, int bf16, int32_t d, int self_loop, hipStream_t s,
                           int64_t n_rows = -1);
 void aggregate_full(reinc_ctx *ctx, const int64_t *ptr, const int32_t *idx, const int32_t *long_rows, int32_t n_long,

@@ -1,12 +1,11 @@
 // Neighbourhood aggregation kernels (paper Section 3.2).
 //
-//   aggregate_long_rows : Eq. 1, from scratch, rows with more than kLongRow entries (power-law hubs): a 4-wave
+//   aggregate_rows : Eq. 1, from scratch.  Rows with more than kLongRow entries (power-law hubs; long_row): a 4-wave
 //       block per row with an LDS reduction.  A wave loads 64 column indices at a time with one coalesced
 //       read and hands them round with lane shuffles; a row of d values is read by LPR = d*sizeof(elem)/16
 //       lanes as one 16-byte load each, so 64/LPR source rows are in flight per load instruction and U of
-//       those instructions are issued back to back.
-//   aggregate_rows_grouped : the same sums with one row per group of LPR lanes, for rows of at most kLongRow
-//       entries (the bulk of a power-law graph): more independent chains per wave.
+//       those instructions are issued back to back.  Rows of at most kLongRow entries (the bulk of a power-law graph;
+//       short_rows): one row per group of LPR lanes, more independent chains per wave.
 //   incremental_segmented : Eq. 2 in the form  S_t[r] = S_{t-1}[r] + sum_ins Y_{t-1}[u] - sum_del Y_{t-1}[u]
 //       + sum_changed dY[u]  over signed tagged entries, the work of a block of rows split by entries.
 //
@@ -139,14 +138,11 @@ __device__ inline void reduce_groups(float (&acc)[VEC])
 // row-pointer -> column-id -> source-row chains in flight and writes with all 64 lanes.  Rows longer than
 // kLongRow are left to the block path.
 template <int LPR, bool BF16>
-__global__ void __launch_bounds__(64 * kWavesPerBlock)
-aggregate_rows_grouped(AggBatch batch, int64_t n, int self_loop)
+__device__ __forceinline__ void short_rows(const AggItem &it, int64_t block, int64_t n, int self_loop)
 {
     constexpr int VEC = Row<BF16>::kVec;
     constexpr int D = LPR * VEC;
     constexpr int G = 64 / LPR;
-    // blockIdx.y picks the snapshot of the batch: its graph, its input and its output
-    const AggItem &it = batch.item[blockIdx.y];
     const int64_t *__restrict__ ptr = it.ptr;
     const int32_t *__restrict__ idx = it.idx;
     const void *__restrict__ X = it.X;
@@ -158,7 +154,7 @@ aggregate_rows_grouped(AggBatch batch, int64_t n, int self_loop)
     const int skip_long = it.n_long > 0;
     const int lane = threadIdx.x & 63;
     const int g = lane / LPR, li = lane % LPR, gbase = g * LPR;
-    const int64_t slot = (int64_t(blockIdx.x) * kWavesPerBlock + (threadIdx.x >> 6)) * G + g;
+    const int64_t slot = (block * kWavesPerBlock + (threadIdx.x >> 6)) * G + g;
     const bool live = slot < n;
     // with an order list the groups of a wavefront take rows of (nearly) equal length
     const int64_t v = live && it.order ? int64_t(it.order[slot]) : slot;
@@ -257,14 +253,12 @@ aggregate_rows_grouped(AggBatch batch, int64_t n, int self_loop)
 
 // one block of kWavesPerBlock waves per long row; wave w takes the 64-entry chunks w, w+4, ...
 template <int LPR, bool BF16>
-__global__ void __launch_bounds__(64 * kWavesPerBlock)
-aggregate_long_rows(AggBatch batch, int self_loop)
+__device__ __forceinline__ void long_row(const AggItem &it, int block, int self_loop)
 {
     constexpr int VEC = Row<BF16>::kVec;
     constexpr int D = LPR * VEC;
     __shared__ float part[kWavesPerBlock][D];
-    const AggItem &it = batch.item[blockIdx.y];
-    if (int(blockIdx.x) >= it.n_long) return;  // the grid is as wide as the batch's longest list
+    if (block >= it.n_long) return;  // the grid is as wide as the batch's longest list
     const int64_t *__restrict__ ptr = it.ptr;
     const int32_t *__restrict__ idx = it.idx;
     const void *__restrict__ X = it.X;
@@ -274,7 +268,7 @@ aggregate_long_rows(AggBatch batch, int self_loop)
     const float *__restrict__ add = it.add;
     float *__restrict__ out = it.out;
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const int64_t v = it.long_rows[blockIdx.x];
+    const int64_t v = it.long_rows[block];
     if (it.row_limit > 0 && v >= it.row_limit) return;  // (the same for the whole block)
     const int64_t beg = ptr[v], end = ptr[v + 1];
     float acc[VEC];
@@ -330,6 +324,20 @@ aggregate_long_rows(AggBatch batch, int self_loop)
         }
         store_f32<VEC>(out, v, D, lane, acc);
     }
+}
+
+// Both kinds of rows in one launch, the blocks of the long ones first: they last longest, and the short ones fill the chip
+// behind them, so that only one tail and one launch are paid.  A launch for each kind -> this one: 3e5 rows of 512 bytes with
+// 4.8e6 edges, forward and adjoint, 745 -> 701 us; 1e5 rows of 256 bytes with 1e6 edges 48 -> 40.  blockIdx.y picks the
+// snapshot of the batch: its graph, its input and its output.
+template <int LPR, bool BF16>
+__global__ void __launch_bounds__(64 * kWavesPerBlock) aggregate_rows(AggBatch batch, int64_t n, int long_blocks, int self_loop)
+{
+    const AggItem &it = batch.item[blockIdx.y];
+    if (int(blockIdx.x) < long_blocks)
+        long_row<LPR, BF16>(it, int(blockIdx.x), self_loop);
+    else
+        short_rows<LPR, BF16>(it, int64_t(blockIdx.x) - long_blocks, n, self_loop);
 }
 
 // Rows of S a block of incremental_segmented works on: as many as make a 16 KB tile of fp32 sums (16 rows of 256
@@ -557,7 +565,7 @@ __device__ inline void mm_store(float *out, int32_t *contrib, int64_t v, int d, 
         *reinterpret_cast<int4 *>(contrib + v * d + li * VEC + i) = make_int4(cs[i], cs[i + 1], cs[i + 2], cs[i + 3]);
 }
 
-// From scratch, rows of at most kLongRow entries: one row per group of LPR lanes (see aggregate_rows_grouped).
+// From scratch, rows of at most kLongRow entries: one row per group of LPR lanes (see short_rows).
 // list == nullptr: rows 0 .. count_host-1; else the listed rows (count_dev, if given, points at their number on the
 // device: the rows that the incremental pass handed back).  Longer rows are left to minmax_long_rows.
 // The gathers of a trip are unconditional: a position past the end of the row repeats the row's last entry, which
@@ -890,39 +898,18 @@ inline int lanes_per_row(int32_t d, int bf16)
 }
 
 template <bool BF16>
-void aggregate_dispatch(int lpr, const AggBatch &batch, int64_t n, int self_loop, hipStream_t s, hipEvent_t ev_start,
-                        hipEvent_t ev_stop)
+void aggregate_dispatch(int lpr, const AggBatch &batch, int64_t n, int32_t max_long, int self_loop, hipStream_t s,
+                        hipEvent_t ev_start, hipEvent_t ev_stop)
 {
     const dim3 th(64 * kWavesPerBlock);
 #define REINC_AGG_CASE(L)                                                                                          \
     case L: {                                                                                                      \
         const int64_t rows_per_block = int64_t(kWavesPerBlock) * (64 / L);                                         \
-        const unsigned blocks = unsigned((n + rows_per_block - 1) / rows_per_block);                               \
-        hipExtLaunchKernelGGL((aggregate_rows_grouped<L, BF16>), dim3(blocks, unsigned(batch.count)), th, 0, s,    \
-                              ev_start, ev_stop, 0, batch, n, self_loop);                                          \
+        const unsigned blocks = unsigned(max_long) + unsigned((n + rows_per_block - 1) / rows_per_block);          \
+        hipExtLaunchKernelGGL((aggregate_rows<L, BF16>), dim3(blocks, unsigned(batch.count)), th, 0, s, ev_start,  \
+                              ev_stop, 0, batch, n, int(max_long), self_loop);                                     \
         break;                                                                                                     \
     }
-    switch (lpr) {
-        REINC_AGG_CASE(1)
-        REINC_AGG_CASE(2)
-        REINC_AGG_CASE(4)
-        REINC_AGG_CASE(8)
-        REINC_AGG_CASE(16)
-        REINC_AGG_CASE(32)
-        REINC_AGG_CASE(64)
-    }
-#undef REINC_AGG_CASE
-}
-
-template <bool BF16>
-void aggregate_long_dispatch(int lpr, const AggBatch &batch, int32_t max_long, int self_loop, hipStream_t s)
-{
-    const dim3 th(64 * kWavesPerBlock);
-    const dim3 grid(unsigned(max_long), unsigned(batch.count));
-#define REINC_AGG_CASE(L)                                                         \
-    case L:                                                                       \
-        aggregate_long_rows<L, BF16><<<grid, th, 0, s>>>(batch, self_loop);       \
-        break;
     switch (lpr) {
         REINC_AGG_CASE(1)
         REINC_AGG_CASE(2)
@@ -1026,6 +1013,8 @@ void launch_aggregate_batch(const AggBatch &batch, int bf16, int32_t d, int64_t 
 {
     if (n <= 0 || batch.count <= 0) return;
     const int lpr = lanes_per_row(d, bf16);
+    int32_t max_long = 0;
+    for (int i = 0; i < batch.count; ++i) max_long = std::max(max_long, batch.item[i].n_long);
     // Rows by falling length (AggItem::order) keep the lane groups of a wavefront equally busy.  That pays while the
     // gathered matrix stays in the caches and the kernel is bound by what a wavefront has in flight (100 000 rows of
     // 256 bytes: 154 -> 140 us per launch of eight snapshots); on matrices far beyond the caches the kernel is bound
@@ -1040,31 +1029,16 @@ void launch_aggregate_batch(const AggBatch &batch, int bf16, int32_t d, int64_t 
         use = &plain;
     }
     if (bf16)
-        aggregate_dispatch<true>(lpr, *use, n, self_loop, s, ev_start, ev_stop);
+        aggregate_dispatch<true>(lpr, *use, n, max_long, self_loop, s, ev_start, ev_stop);
     else
-        aggregate_dispatch<false>(lpr, *use, n, self_loop, s, ev_start, ev_stop);
-}
-
-void launch_aggregate_long_batch(const AggBatch &batch, int bf16, int32_t d, int self_loop, hipStream_t s)
-{
-    int32_t max_long = 0;
-    for (int i = 0; i < batch.count; ++i) max_long = std::max(max_long, batch.item[i].n_long);
-    if (max_long <= 0) return;
-    const int lpr = lanes_per_row(d, bf16);
-    if (bf16)
-        aggregate_long_dispatch<true>(lpr, batch, max_long, self_loop, s);
-    else
-        aggregate_long_dispatch<false>(lpr, batch, max_long, self_loop, s);
+        aggregate_dispatch<false>(lpr, *use, n, max_long, self_loop, s, ev_start, ev_stop);
 }
 
 void aggregate_full_batch(reinc_ctx *ctx, const AggBatch &batch, int bf16, int32_t d, int self_loop, hipStream_t s, int64_t n_rows)
 {
-    {
-        // the timing events ride on the launch itself, so they carry the kernel's own begin and end
-        ProfScope prof(ctx, REINC_K_AGG_FULL, s, true);
-        launch_aggregate_batch(batch, bf16, d, n_rows >= 0 ? n_rows : ctx->cfg.num_nodes, self_loop, s, prof.start(), prof.stop());
-    }
-    launch_aggregate_long_batch(batch, bf16, d, self_loop, s);
+    // the timing events ride on the launch itself, so they carry the kernel's own begin and end
+    ProfScope prof(ctx, REINC_K_AGG_FULL, s, true);
+    launch_aggregate_batch(batch, bf16, d, n_rows >= 0 ? n_rows : ctx->cfg.num_nodes, self_loop, s, prof.start(), prof.stop());
 }
 
 void aggregate_full(reinc_ctx *ctx, const int64_t *ptr, const int32_t *idx, const int32_t *long_rows, int32_t n_long,
