@@ -81,6 +81,7 @@ struct AggItem {
     const int32_t *long_rows;
     int32_t n_long;
     int64_t row_limit = 0;  // > 0: listed long rows from this row on are skipped (their output rows do not exist)
+    int64_t src_limit = 0;  // > 0: X has this many rows, the sources from there on are zero rows
     const int32_t *order = nullptr;  // [n] or null: the row the i-th lane group of the short-row kernel takes
     const float *bias = nullptr;     // [d] or null: added to the scaled row (before relu, mask and add)
     int relu = 0;                    // clamp at zero after the bias

@@ -12,6 +12,7 @@
 // No atomics anywhere: every output row has one writer and a fixed summation order, so results are
 // bit-reproducible from run to run.
 #include <algorithm>
+#include <climits>
 
 #include "ctx.h"
 
@@ -83,7 +84,7 @@ __device__ inline void store_f32(float *base, int64_t row, int d, int li, const 
 // Sums in_scale[u] * X[u] over the entries [beg, end) handled by this wave (entry e goes to lane group e % G).
 template <int LPR, bool BF16>
 __device__ inline void gather_segment(const int32_t *idx, int64_t beg, int64_t end, int64_t stride, const void *X,
-                                      const float *in_scale, int d, int lane, float (&acc)[Row<BF16>::kVec])
+                                      const float *in_scale, int32_t src_limit, int d, int lane, float (&acc)[Row<BF16>::kVec])
 {
     constexpr int VEC = Row<BF16>::kVec;
     constexpr int G = 64 / LPR;
@@ -95,6 +96,7 @@ __device__ inline void gather_segment(const int32_t *idx, int64_t beg, int64_t e
         if (lane < cnt) {
             my_u = idx[base + lane];
             if (in_scale) my_sc = in_scale[my_u];
+            if (my_u >= src_limit) my_u = -1;
         }
         for (int k = 0; k < cnt; k += G * kSumUnroll<BF16>) {
             float r[kSumUnroll<BF16>][VEC];
@@ -104,7 +106,7 @@ __device__ inline void gather_segment(const int32_t *idx, int64_t beg, int64_t e
             for (int j = 0; j < kSumUnroll<BF16>; ++j) {
                 const int e = k + j * G + g;
                 const int32_t u = __shfl(my_u, e & 63);
-                if (e < cnt) {
+                if (e < cnt && u >= 0) {
                     Row<BF16>::load(X, u, d, li, r[j]);
                 } else {
 #pragma unroll
@@ -151,6 +153,7 @@ __device__ __forceinline__ void short_rows(const AggItem &it, int64_t block, int
     const float *__restrict__ mask = it.mask;
     const float *__restrict__ add = it.add;
     float *__restrict__ out = it.out;
+    const int32_t src_limit = it.src_limit > 0 ? int32_t(it.src_limit) : INT_MAX;
     const int skip_long = it.n_long > 0;
     const int lane = threadIdx.x & 63;
     const int g = lane / LPR, li = lane % LPR, gbase = g * LPR;
@@ -183,6 +186,7 @@ __device__ __forceinline__ void short_rows(const AggItem &it, int64_t block, int
         if (li < cnt) {
             my_u = idx[beg + base + li];
             if (in_scale) my_sc = in_scale[my_u];
+            if (my_u >= src_limit) my_u = -1;
         }
         const int cmax = min(LPR, maxlen - base);
         for (int k = 0; k < cmax; k += kSumUnroll<BF16>) {
@@ -192,7 +196,7 @@ __device__ __forceinline__ void short_rows(const AggItem &it, int64_t block, int
             for (int j = 0; j < kSumUnroll<BF16>; ++j) {
                 const int e = k + j;
                 const int32_t u = __shfl(my_u, gbase + (e & (LPR - 1)));
-                if (e < cnt) {
+                if (e < cnt && u >= 0) {
                     Row<BF16>::load(X, u, D, li, r[j]);
                 } else {
 #pragma unroll
@@ -212,7 +216,7 @@ __device__ __forceinline__ void short_rows(const AggItem &it, int64_t block, int
         }
     }
     if (live && !skipped) {
-        if (self_loop) {
+        if (self_loop && v < src_limit) {
             float r[VEC];
             Row<BF16>::load(X, v, D, li, r);
             const float sc = in_scale ? in_scale[v] : 1.0f;
@@ -267,6 +271,7 @@ __device__ __forceinline__ void long_row(const AggItem &it, int block, int self_
     const float *__restrict__ mask = it.mask;
     const float *__restrict__ add = it.add;
     float *__restrict__ out = it.out;
+    const int32_t src_limit = it.src_limit > 0 ? int32_t(it.src_limit) : INT_MAX;
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int64_t v = it.long_rows[block];
     if (it.row_limit > 0 && v >= it.row_limit) return;  // (the same for the whole block)
@@ -274,7 +279,7 @@ __device__ __forceinline__ void long_row(const AggItem &it, int block, int self_
     float acc[VEC];
 #pragma unroll
     for (int i = 0; i < VEC; ++i) acc[i] = 0.0f;
-    gather_segment<LPR, BF16>(idx, beg + 64 * w, end, 64 * kWavesPerBlock, X, in_scale, D, lane, acc);
+    gather_segment<LPR, BF16>(idx, beg + 64 * w, end, 64 * kWavesPerBlock, X, in_scale, src_limit, D, lane, acc);
     reduce_groups<LPR, VEC>(acc);
     if (lane < LPR)
 #pragma unroll
@@ -287,7 +292,7 @@ __device__ __forceinline__ void long_row(const AggItem &it, int block, int self_
             for (int k = 1; k < kWavesPerBlock; ++k) s += part[k][lane * VEC + i];
             acc[i] = s;
         }
-        if (self_loop) {
+        if (self_loop && v < src_limit) {
             float r[VEC];
             Row<BF16>::load(X, v, D, lane, r);
             const float sc = in_scale ? in_scale[v] : 1.0f;
