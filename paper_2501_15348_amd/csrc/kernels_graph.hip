@@ -599,52 +599,67 @@ __device__ inline uint32_t block_prefix_u32(uint32_t v, uint32_t *wave_sums, uin
     return before + incl - v;
 }
 
-// set bits of the flag words in [from, to)
-__device__ inline int rank_bits(const uint64_t *mask, int from, int to)
+// set bits of the flag words before entry e; before: set bits of the words in front of each word
+__device__ inline int bits_before(const uint64_t *mask, const int32_t *before, int e)
 {
-    const int w1 = to >> 6;
-    int w = from >> 6;
-    if (w == w1) return __popcll((mask[w] >> (from & 63)) & ((uint64_t(1) << (to - from)) - 1));
-    int k = __popcll(mask[w] >> (from & 63));
-    for (++w; w < w1; ++w) k += __popcll(mask[w]);
-    return (to & 63) ? k + __popcll(mask[w1] & ((uint64_t(1) << (to & 63)) - 1)) : k;
+    const int w = e >> 6;
+    return before[w] + __popcll(mask[w] & ((uint64_t(1) << (e & 63)) - 1));
 }
 
-// Pass 2 over one list of at most kDiffCap entries: an entry's place in the output is where its row begins there plus the
-// number of set flag bits between the row's first entry and it -- a word or two, at most 32 -- so every flagged entry
-// finds its place by itself and nothing in the block waits for anything else.  The columns a thread may need are
-// requested kFillAhead at a time, flagged or not (every line of the list is touched either way).  5 pairs of 5e5 rows and
-// 6e6 entries, 10 % of them flagged: 277 us; with prefix sums over the block's flags (the form below) 347.
-constexpr int kFillAhead = 4;
-
-template <bool IS_B>
-__device__ inline void diff_fill_ranked(const DiffStep &st, const int32_t *mine, const int32_t *off_mine, int nr, const uint64_t *mask_absent,
-                                        const uint64_t *mask_hit, const int32_t *p_ins, const int32_t *p_del, const int32_t *p_ent,
-                                        int64_t out0, int64_t ent0)
+// the k-th set bit of a word that has more than k
+__device__ inline int select_bit(uint64_t word, int k)
 {
-    const int total = off_mine[nr];
-    for (int base = threadIdx.x; base < total; base += kFillAhead * kDiffThreads) {
-        int32_t us[kFillAhead];
+    uint32_t half = uint32_t(word);
+    int at = 0, low = __popc(half);
+    if (k >= low) k -= low, at = 32, half = uint32_t(word >> 32);
 #pragma unroll
-        for (int q = 0; q < kFillAhead; ++q) us[q] = mine[min(base + q * kDiffThreads, total - 1)];
+    for (int width = 16; width > 0; width >>= 1) {
+        low = __popc(half & ((1u << width) - 1u));
+        if (k >= low) k -= low, at += width, half >>= width;
+    }
+    return at;
+}
+
+// Pass 2 over a block's lists of at most kDiffCap entries.  The flagged entries of the three kinds (inserted, feature change,
+// deleted) are numbered by their flag bits, and thread k takes the k-th: it finds its word in the words' prefix sums and its
+// bit by halving.  The number is also the place in the insert or delete list; in the merged rows the place within the row is
+// the number less the row's first.  (A thread per entry of the lists, a tenth of them flagged, did the same work with a
+// tenth of its lanes: 5 pairs of 5e5 rows and 6e6 entries 281 us, this 155.)
+constexpr int kDiffWords = kDiffCap / 64;
+
+__device__ inline void diff_fill_flagged(const DiffStep &st, const int32_t *offa, const int32_t *offb, int nr,
+                                         const uint64_t (&flags)[3][kDiffWords], const int32_t (&before)[3][kDiffWords + 1],
+                                         const int32_t *cols_a, const int32_t *cols_b, const int32_t *p_ins, const int32_t *p_del,
+                                         const int32_t *p_ent, int64_t ins0, int64_t del0, int64_t ent0)
+{
+    const int n_ins = before[0][kDiffWords], n_hit = before[1][kDiffWords], n_del = before[2][kDiffWords];
+    for (int i = threadIdx.x; i < n_ins + n_hit + n_del; i += kDiffThreads) {
+        const int kind = i < n_ins ? 0 : i < n_ins + n_hit ? 1 : 2, k = i - (kind == 0 ? 0 : kind == 1 ? n_ins : n_ins + n_hit);
+        const int32_t *pre = before[kind];
+        int w = 0;
 #pragma unroll
-        for (int q = 0; q < kFillAhead; ++q) {
-            const int e = base + q * kDiffThreads;
-            if (e >= total) break;
-            const bool absent = (mask_absent[e >> 6] >> (e & 63)) & 1, hit = IS_B && mask_hit && ((mask_hit[e >> 6] >> (e & 63)) & 1);
-            if (!absent && !hit) continue;
-            const int32_t u = us[q];
-            const int r = row_of(off_mine, nr, e), first = off_mine[r];
-            const int n_ins = p_ins[r + 1] - p_ins[r];
-            if (absent) {
-                const int k = rank_bits(mask_absent, first, e);
-                (IS_B ? st.ins_col : st.del_col)[out0 + (IS_B ? p_ins : p_del)[r] + k] = u;
-                st.ent[ent0 + p_ent[r] + (IS_B ? 0 : n_ins) + k] = (IS_B ? 0u : 1u << kKindShift) | uint32_t(u);
-            }
-            if (hit)
-                st.ent[ent0 + p_ent[r] + n_ins + (p_del[r + 1] - p_del[r]) + rank_bits(mask_hit, first, e)] =
-                    (2u << kKindShift) | uint32_t(st.coffs[u]);
+        for (int step = kDiffWords / 2; step > 0; step >>= 1)
+            if (pre[w + step] <= k) w += step;
+        const int e = 64 * w + select_bit(flags[kind][w], k - pre[w]);
+        const int32_t u = (kind == 2 ? cols_a : cols_b)[e];
+        const int32_t *off = kind == 2 ? offa : offb;
+        const int r = row_of(off, nr, e);
+        const int ins_r = p_ins[r], ins_n = p_ins[r + 1] - ins_r, del_r = p_del[r];
+        int64_t at = ent0 + p_ent[r];
+        uint32_t entry;
+        if (kind == 0) {
+            st.ins_col[ins0 + k] = u;
+            at += k - ins_r;
+            entry = uint32_t(u);
+        } else if (kind == 2) {
+            st.del_col[del0 + k] = u;
+            at += ins_n + (k - del_r);
+            entry = (1u << kKindShift) | uint32_t(u);
+        } else {
+            at += ins_n + (p_del[r + 1] - del_r) + (k - bits_before(flags[1], before[1], off[r]));
+            entry = (2u << kKindShift) | uint32_t(st.coffs[u]);
         }
+        st.ent[at] = entry;
     }
 }
 
@@ -741,7 +756,8 @@ __global__ void __launch_bounds__(kDiffThreads) diff_fill(const DiffStep *steps,
     __shared__ int32_t offa[kDiffRows + 1], offb[kDiffRows + 1];
     __shared__ int32_t p_ins[kDiffRows + 1], p_del[kDiffRows + 1], p_ent[kDiffRows + 1], hit_before[kDiffRows + 1];
     __shared__ uint32_t wave_sums[kDiffThreads / 64];
-    __shared__ uint64_t flags[3][kDiffCap / 64];
+    __shared__ uint64_t flags[3][kDiffWords];
+    __shared__ int32_t before[3][kDiffWords + 1];  // set bits of the words in front; [kDiffWords]: of all
     const DiffStep st = steps[blockIdx.y];  // (a copy: the pointers stay in registers across the stores below)
     const int64_t v0 = int64_t(blockIdx.x) * kDiffRows;
     const int nr = int(min(int64_t(kDiffRows), n - v0));
@@ -752,15 +768,23 @@ __global__ void __launch_bounds__(kDiffThreads) diff_fill(const DiffStep *steps,
     const uint64_t *bits = st.coffs[n] > 0 ? st.bits : nullptr;
     const uint64_t *mask_ins = st.mask_ins + mask_base(b0), *mask_del = st.mask_del + mask_base(a0);
     const uint64_t *mask_hit = bits ? st.mask_hit + mask_base(b0) : nullptr;
-    // the flag words of a small block go to LDS together with the row pointers: [inserted | feature change | deleted]
-    if (small) {
-        const int w = threadIdx.x % 64, words_b = int(nb + 63) / 64, words_a = int(na + 63) / 64;
-        if (threadIdx.x < 64) {
-            if (w < words_b) flags[0][w] = mask_ins[w];
-        } else if (threadIdx.x < 128) {
-            if (w < words_b && mask_hit) flags[1][w] = mask_hit[w];
-        } else if (threadIdx.x < 192) {
-            if (w < words_a) flags[2][w] = mask_del[w];
+    // the flag words of a small block go to LDS together with the row pointers: inserted, feature change, deleted; a wavefront
+    // each, which also numbers their bits
+    if (small && threadIdx.x < 3 * 64) {
+        const int kind = threadIdx.x >> 6, w = threadIdx.x & 63;
+        const uint64_t *mask = kind == 0 ? mask_ins : kind == 1 ? mask_hit : mask_del;
+        const int words = int((kind == 2 ? na : nb) + 63) / 64;
+        const uint64_t word = mask && w < words ? mask[w] : 0;
+        int incl = __popcll(word);
+#pragma unroll
+        for (int off = 1; off < kDiffWords; off <<= 1) {
+            const int up = __shfl_up(incl, off);
+            if (w >= off) incl += up;
+        }
+        if (w < kDiffWords) {
+            flags[kind][w] = word;
+            before[kind][w + 1] = incl;
+            if (w == 0) before[kind][0] = 0;
         }
     }
     for (int i = threadIdx.x; i <= nr; i += kDiffThreads) {
@@ -773,8 +797,7 @@ __global__ void __launch_bounds__(kDiffThreads) diff_fill(const DiffStep *steps,
     __syncthreads();
     // only flagged entries are touched, so the column lists are read from global memory (a few scattered words)
     if (small) {
-        diff_fill_ranked<true>(st, st.col_b + b0, offb, nr, flags[0], bits ? flags[1] : nullptr, p_ins, p_del, p_ent, ins0, ent0);
-        if (p_del[nr] > 0) diff_fill_ranked<false>(st, st.col_a + a0, offa, nr, flags[2], nullptr, p_ins, p_del, p_ent, del0, ent0);
+        diff_fill_flagged(st, offa, offb, nr, flags, before, st.col_a + a0, st.col_b + b0, p_ins, p_del, p_ent, ins0, del0, ent0);
     } else {
         diff_fill_hub(st, v0, nr, offa, offb, st.col_a + a0, st.col_b + b0, mask_ins, mask_del, mask_hit, bits, self_loop, p_ins, p_del, p_ent,
                       hit_before, ins0, del0, ent0, wave_sums);
