@@ -159,13 +159,22 @@ def _dev_ptr(t):
         return None
     if not t.is_cuda or not t.is_contiguous():
         raise ValueError("expected a contiguous device tensor")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
+
+
+@functools.lru_cache(maxsize=None)
+def _torch_c():
+    import torch
+
+    torch.cuda.init()
+    return torch._C
 
 
 def _stream():
-    import torch
-
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    """Handle of the current stream of the current device.  (torch.cuda.current_stream() makes an object of it first: 3.0 us of
+    the 10.5 that a small gcn_transform took on the host; this 0.2.)"""
+    c = _torch_c()
+    return c._cuda_getCurrentRawStream(c._cuda_getDevice())
 
 
 class Context:
