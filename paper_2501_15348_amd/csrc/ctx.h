@@ -401,6 +401,13 @@ void launch_rnn_fused(int lstm, const float *x, const float *x_scale, int64_t n,
                       const float *h_carry, const float *c_prev, const float *W_i, const float *W_h, const float *b_i,
                       const float *b_h, float *h_out, float *c_out, float *saved, hipStream_t s);
 bool dense_split_enabled();  // (kernels_dense.hip)
+// ---- kernels_small.hip: few rows.  false, and nothing done: more tiles of 32 rows by 32 columns (units) than these pay
+// for, or an output that lies in an input
+bool launch_gemm_small(const void *A, int a_bf16, int64_t n, int32_t K, int32_t M, const float *row_scale, const float *W,
+                       const float *bias, int relu, float *out, hipStream_t s);
+bool launch_rnn_small(int lstm, const float *x, int64_t n, int32_t d_in, int32_t H, const float *h_prev, const float *c_prev,
+                      const float *W_i, const float *W_h, const float *b_i, const float *b_h, float *h_out, float *c_out, float *saved,
+                      hipStream_t s);
 // ---- kernels_planes.hip: dense products on two fp16 planes per operand
 constexpr int kMaxPlaneK = 512;  // deepest product (padded; of a recurrent step: x and h together)
 constexpr int plane_pad(int k) { return (k + 31) & ~31; }

@@ -539,6 +539,14 @@ int reinc_gcn_transform_work(reinc_ctx *ctx, const void *A, int a_dtype, int64_t
         }
         prof.drop();
     }
+    if (reinc_gcn_work_bytes(n, d_in, d_out) == 0) {  // (with or without a work area: the plane kernels have the others)
+        ProfScope prof(ctx, REINC_K_GEMM_ROWS, as_stream(stream));
+        if (launch_gemm_small(A, int(a_dtype == REINC_BF16), n, d_in, d_out, row_scale, W, b, relu, out, as_stream(stream))) {
+            REINC_HIP(ctx, hipGetLastError());
+            return REINC_OK;
+        }
+        prof.drop();
+    }
     gemm_rows(ctx, as_stream(stream), A, int(a_dtype == REINC_BF16), n, d_in, d_out, row_scale, W, 0, d_out, b, relu,
               (const float *)nullptr, (const float *)nullptr, out);
     REINC_HIP(ctx, hipGetLastError());
@@ -579,6 +587,15 @@ int reinc_rnn_step_work(reinc_ctx *ctx, int rnn_kind, const float *x, int64_t n,
         launch_prepare_planes(jobs, as_stream(stream));
         if (launch_rnn_planes(jobs.job[0], lstm, x, nullptr, n, h_prev, lstm ? c_prev : h_prev, b_i, b_h, h_out, c_out, saved,
                               as_stream(stream))) {
+            REINC_HIP(ctx, hipGetLastError());
+            return REINC_OK;
+        }
+        prof.drop();
+    }
+    if (reinc_rnn_work_bytes(rnn_kind, n, d_in, H) == 0) {
+        ProfScope prof(ctx, REINC_K_RNN, as_stream(stream));
+        if (launch_rnn_small(int(rnn_kind == REINC_RNN_LSTM), x, n, d_in, H, h_prev, c_prev, W_i, W_h, b_i, b_h, h_out, c_out, saved,
+                             as_stream(stream))) {
             REINC_HIP(ctx, hipGetLastError());
             return REINC_OK;
         }
