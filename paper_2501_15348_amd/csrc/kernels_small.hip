@@ -239,7 +239,7 @@ bool launch_rnn_small(int lstm, const float *x, int64_t n, int32_t d_in, int32_t
                       const float *W_i, const float *W_h, const float *b_i, const float *b_h, float *h_out, float *c_out, float *saved,
                       hipStream_t s)
 {
-    if (n <= 0 || H > 32 * 65535 || (d_in + H <= kMaxPlaneK && tiles(n, H) > kSmallRnnTiles)) return false;
+    if (n <= 0 || H > 32 * 65535 || (plane_pad(d_in) + plane_pad(H) <= kMaxPlaneK && tiles(n, H) > kSmallRnnTiles)) return false;
     for (const float *in : {x, h_prev})
         for (const float *out : {h_out, c_out, saved})
             if (!apart(out, n * H * (out == saved ? 4 : 1), in, 4 * n * (in == x ? d_in : H))) return false;
