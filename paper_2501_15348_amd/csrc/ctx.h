@@ -388,10 +388,10 @@ void launch_incremental(const int32_t *rows, const int64_t *row_ent, int64_t n_r
 
 // ---- kernels_dense.hip
 // out[n,M] = epilogue((row_scale .* A)[n,K] * B[K,M]); B = W (ldw = row stride) or W^T when w_transposed.
-// epilogue: + bias, relu, + add[n,M], zero where mask[n,M] <= 0 (each optional)
+// epilogue: + bias, relu, + add[n,M], zero where mask[n,M] <= 0 (each optional).  lda: from a row of A to the next (0: K)
 int launch_gemm_rows(const void *A, int a_bf16, int64_t n, int32_t K, int32_t M, const float *row_scale, const float *W,
                      int w_transposed, int32_t ldw, const float *bias, int relu, const float *add, const float *mask,
-                     float *out, hipStream_t s);
+                     float *out, hipStream_t s, int32_t lda = 0);
 // db[j] (+)= sum over the n rows of G[., j]; partial: scratch of column_sums_bytes(M); fixed summation order
 uint64_t column_sums_bytes(int32_t M);
 void launch_column_sums(const float *G, int64_t n, int32_t M, float *partial, float *db, int accumulate, hipStream_t s);
@@ -465,8 +465,9 @@ struct RnnBackward {
     float *carry_out;      // GRU, one step: receives dh .* z, which is then left out of `out`; or null
     float *out;            // gradient w.r.t. the state before the earliest step (may be dh)
 };
-bool rnn_backward_planes_shape(int32_t H);
 bool rnn_backward_exact(int lstm, int32_t H);
+// whether the launch takes this width, without and with dz: asked before the gate gradients are laid out its way
+bool rnn_backward_planes_ready(int lstm, int32_t H, bool input);
 bool launch_rnn_backward_planes(const PlaneJob *wh, const PlaneJob *wi, int lstm, const RnnBackward &b, hipStream_t s);
 uint64_t reduce_partial_bytes(int64_t n, int32_t K, int32_t M);
 // partial[chunk] (+)= (row_scale .* A)^T G over the chunk's rows, with the column sums of G in row K; `accumulate`

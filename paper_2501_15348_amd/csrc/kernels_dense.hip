@@ -1949,10 +1949,11 @@ __global__ void fill_f32_kernel(float *p, int64_t n, float v)
 
 int launch_gemm_rows(const void *A, int a_bf16, int64_t n, int32_t K, int32_t M, const float *row_scale, const float *W,
                      int w_transposed, int32_t ldw, const float *bias, int relu, const float *add, const float *mask,
-                     float *out, hipStream_t s)
+                     float *out, hipStream_t s, int32_t lda)
 {
     if (n <= 0) return 0;
-    GemmArgs g{A, n, K, M, K, row_scale, W, ldw, w_transposed, bias, relu, mask, add, out};
+    if (lda == 0) lda = K;
+    GemmArgs g{A, n, K, M, lda, row_scale, W, ldw, w_transposed, bias, relu, mask, add, out};
     // Deep products (K = 512: the gate gradients of an LSTM times W^T) whose three-plane slab fits for half of K only:
     // two passes over the halves of K, the second adding to the first (out = A1 W1 + add, then out = A2 W2 + out).
     // Without bias and ReLU the epilogue order (add, then mask) makes the two passes equal to the single product.
@@ -1962,8 +1963,8 @@ int launch_gemm_rows(const void *A, int a_bf16, int64_t n, int32_t K, int32_t M,
         const int half = K / 2;
         const char *A2 = static_cast<const char *>(A) + size_t(half) * (a_bf16 ? 2 : 4);
         const float *W2 = w_transposed ? W + half : W + int64_t(half) * ldw;
-        GemmArgs g1{A, n, half, M, K, row_scale, W, ldw, w_transposed, nullptr, 0, nullptr, add, out};
-        GemmArgs g2{A2, n, half, M, K, row_scale, W2, ldw, w_transposed, nullptr, 0, mask, out, out};
+        GemmArgs g1{A, n, half, M, lda, row_scale, W, ldw, w_transposed, nullptr, 0, nullptr, add, out};
+        GemmArgs g2{A2, n, half, M, lda, row_scale, W2, ldw, w_transposed, nullptr, 0, mask, out, out};
         if (gemm_rows_resident_dispatch(g1, a_bf16, s)) {
             if (gemm_rows_resident_dispatch(g2, a_bf16, s)) return 0;
             return -1;  // cannot happen: the second pass has the shape of the first

@@ -62,16 +62,15 @@ struct Planes {
     void prepare(hipStream_t s) const { launch_prepare_planes(jobs, s); }
 };
 
-// out[n,M] = epilogue((row_scale .* A)[n,K] * B[K,M]) with B = W or W^T, prepared (w) or not
+// out[n,M] = epilogue((row_scale .* A)[n,K] * B[K,M]) with B = W or W^T, prepared (w) or not; lda: from a row of A to the
+// next (0: K)
 void product(reinc_ctx *ctx, hipStream_t st, const PlaneJob *w, const float *A, int64_t n, int K, int M, const float *row_scale,
              const float *W, int wT, int ldw, const float *bias, int relu, const float *add, const float *mask, float *out, int lda = 0)
 {
     ProfScope prof(ctx, REINC_K_GEMM_ROWS, st);
-    const bool apart = lda > K;  // (rows that lie apart are for the plane kernel)
-    if (w && (apart || planes_pay_backward(n, K, M)) &&
-        launch_gemm_planes(*w, A, 0, n, apart ? lda : K, row_scale, bias, relu, add, mask, out, st))
-        return;
-    launch_gemm_rows(A, 0, n, K, M, row_scale, W, wT, ldw, bias, relu, add, mask, out, st);
+    if (lda == 0) lda = K;
+    if (w && planes_pay_backward(n, K, M) && launch_gemm_planes(*w, A, 0, n, lda, row_scale, bias, relu, add, mask, out, st)) return;
+    launch_gemm_rows(A, 0, n, K, M, row_scale, W, wT, ldw, bias, relu, add, mask, out, st, lda);
 }
 
 // one recurrent step; see launch_rnn_fused
@@ -816,6 +815,9 @@ int reinc_backward_window(reinc_ctx *ctx, int32_t t0, int32_t L, const float *pa
         for (int l = 1; l <= Lg; ++l) b += align256(reduce_partial_bytes(int64_t(rows), c.dims[l - 1], c.dims[l]));
         return b + align256(column_sums_bytes(maxd));
     };
+    // all steps of a batch back in time in one launch, which keeps a GRU's gate gradients as one array of 4 H columns
+    bool chain = rnn_backward_planes_ready(lstm, H, false);
+    const bool exact = rnn_backward_exact(lstm, H);  // (no planes needed)
     // the transposed weights come before the depth of a batch, but not before a batch of one timestep
     Planes planes;
     int plane_whT = -1, plane_wiT = -1, plane_wT[REINC_MAX_GCN_LAYERS + 1] = {-1, -1, -1, -1};
@@ -825,6 +827,7 @@ int reinc_backward_window(reinc_ctx *ctx, int32_t t0, int32_t L, const float *pa
         return planes.add(ctx->scratch(bytes), W, nullptr, K, 0, K, 1, 1, M);
     };
     plane_whT = prepared(p.W_h, KH, H);
+    chain = chain && (exact || plane_whT >= 0);
     plane_wiT = prepared(p.W_i, KH, c.dims[Lg]);
     for (int l = 2; l <= Lg; ++l) plane_wT[l] = prepared(p.W[l], c.dims[l], c.dims[l - 1]);
     const uint64_t free_bytes = ok ? ctx->top - ctx->bottom : 0;
@@ -836,10 +839,10 @@ int reinc_backward_window(reinc_ctx *ctx, int32_t t0, int32_t L, const float *pa
     }
     const int64_t rowsB = int64_t(B) * n;
     const int64_t rowsT = int64_t(B) * nt;  // rows of a batch of timesteps in the top quantities
-    // all steps of a batch back in time in one launch, which keeps a GRU's gate gradients as one array of 4 H columns
-    const bool chain = rnn_backward_planes_shape(H) && (rnn_backward_exact(lstm, H) || (plane_whT >= 0 && plane_wiT >= 0));
-    // ... unless one of the kinds of work that this launch does is being timed: then they are launched apart
-    const bool apart = chain && plane_wiT >= 0 && (ctx->prof_mask & (1u << REINC_K_ELEM | 1u << REINC_K_GEMM_ROWS));
+    // ... and with the input's gradient, unless one of the kinds of work that this launch does is being timed: then the
+    // steps and the product with W_i^T are launched apart
+    const bool timed = ctx->prof_mask & (1u << REINC_K_ELEM | 1u << REINC_K_GEMM_ROWS);
+    const bool input = chain && !timed && (exact || plane_wiT >= 0) && rnn_backward_planes_ready(lstm, H, true);
     const int ldg = chain ? 4 * H : KH;
     float *dgi = f32(uint64_t(rowsB) * ldg);
     float *dgh = lstm || chain ? dgi : f32(uint64_t(rowsB) * ldg);
@@ -883,31 +886,20 @@ int reinc_backward_window(reinc_ctx *ctx, int32_t t0, int32_t L, const float *pa
         const int nb = hi - lo + 1;
         const int dl = c.dims[Lg];
         // the recurrent chain of the batch, last timestep first
-        if (chain) {
-            const LocalStep &st = ctx->local[hi], &pv = ctx->local[std::max(hi - 1, 0)];
+        const int each = timed ? 1 : nb;  // timesteps of a launch
+        for (int32_t i = hi; i >= lo && chain; i -= each) {
+            const LocalStep &st = ctx->local[i], &pv = ctx->local[std::max(i - 1, 0)];
             RnnBackward b{};
-            b.n = nt, b.H = H, b.d = dl, b.steps = nb, b.to_first = lo == 0;
+            b.n = nt, b.H = H, b.d = dl, b.steps = each, b.to_first = i - each + 1 == 0;
             b.W_h = p.W_h, b.W_i = p.W_i;
             b.dh = dh, b.dc = dc_in, b.saved = st.saved, b.h_prev = pv.h, b.c_prev = pv.c, b.c_new = st.c;
-            b.dg = dgi + int64_t(nb - 1) * nt * ldg;
-            b.mask = st.H[Lg], b.dz = dz + int64_t(nb - 1) * nt * dl;
+            b.dg = dgi + int64_t(i - lo) * nt * ldg;
+            if (input) b.mask = st.H[Lg], b.dz = dz + int64_t(i - lo) * nt * dl;
             b.saved_step = int64_t(slice_floats(nt, 4 * H)), b.state_step = int64_t(slice_floats(nt, H));
             b.dg_step = nt * ldg, b.mask_step = int64_t(slice_floats(nt, dl)), b.dz_step = nt * dl;
             b.dc_out = dc, b.out = dh;
-            if (apart) {
-                b.dz = nullptr, b.steps = 1;
-                for (int32_t i = hi; i >= lo; --i) {
-                    const LocalStep &si = ctx->local[i], &before = ctx->local[std::max(i - 1, 0)];
-                    b.to_first = i == 0, b.dc = dc_in;
-                    b.saved = si.saved, b.h_prev = before.h, b.c_prev = before.c, b.c_new = si.c;
-                    b.dg = dgi + int64_t(i - lo) * nt * ldg;
-                    REINC_TRY(rnn_backward_steps(ctx, s, planes.get(plane_whT), nullptr, lstm, b));
-                    if (lstm) dc_in = dc;
-                }
-            } else {
-                REINC_TRY(rnn_backward_steps(ctx, s, planes.get(plane_whT), planes.get(plane_wiT), lstm, b));
-                if (lstm) dc_in = dc;
-            }
+            REINC_TRY(rnn_backward_steps(ctx, s, planes.get(plane_whT), planes.get(plane_wiT), lstm, b));
+            if (lstm) dc_in = dc;
         }
         for (int32_t i = hi; i >= lo && !chain; --i) {
             const LocalStep &st = ctx->local[i];
@@ -947,7 +939,7 @@ int reinc_backward_window(reinc_ctx *ctx, int32_t t0, int32_t L, const float *pa
             return REINC_OK;
         }));
         // gradient w.r.t. the last GCN layer's pre-activation, all timesteps of the batch
-        if (!chain || apart) REINC_TRY(for_runs(lo, hi, nt, {Strip{Ap.data(), dl}}, [&](int i0, int len) {
+        if (!input) REINC_TRY(for_runs(lo, hi, nt, {Strip{Ap.data(), dl}}, [&](int i0, int len) {
             product(ctx, s, planes.get(plane_wiT), dgi + int64_t(i0 - lo) * nt * ldg, nt * len, KH, dl, nof, p.W_i, 1, KH, nof, 0, nof,
                     Ap[i0], dz + int64_t(i0 - lo) * nt * dl, ldg);
             return REINC_OK;
@@ -1150,7 +1142,7 @@ int reinc_backward_window_integrated(reinc_ctx *ctx, int32_t t0, int32_t L, cons
         return ctx->fail(REINC_E_NOMEM, "arena exhausted: no room for the backward scratch buffers");
     }
     const int64_t rowsB = int64_t(B) * n;
-    const bool fused = rnn_backward_planes_shape(H) && (rnn_backward_exact(lstm, H) || plane_whT >= 0);  // (see reinc_backward_window)
+    const bool fused = rnn_backward_planes_ready(lstm, H, false) && (rnn_backward_exact(lstm, H) || plane_whT >= 0);  // (see reinc_backward_window)
     const int ldg = fused ? 4 * H : KH, gap_at = fused && !lstm ? 2 * H : INT_MAX;
     float *dgi = f32(uint64_t(rowsB) * ldg);
     float *dgh = lstm || fused ? dgi : f32(uint64_t(rowsB) * ldg);

@@ -526,3 +526,47 @@ def test_steps_of_a_window_in_one_launch(rnn, n, hidden, top):
                            lambda sv: oracle.backward_window(graphs, sv, ref_h, p, 1, wl.agg, wl.self_loop, rnn, target),
                            [name for name, _ in synth.param_shapes(wl)], GRAD_RTOL_FP32)
     ctx.close()
+
+
+# A backward pass whose scratch holds the prepared W_h^T but not W_i^T keeps the steps that make gate gradients and their
+# product with W_h^T together, and multiplies with W_i as it is (a GRU's gate gradients lie 4 H apart, 3 H wide).
+@pytest.mark.parametrize("rnn", ["gru", "lstm"])
+def test_backward_with_room_for_the_recurrent_weights_alone(rnn):
+    import torch
+
+    from paper_2501_15348_amd import reinc, synth
+
+    length, hidden = 3, 64
+    wl = synth.WORKLOADS["c3"].scaled(65, length, dims=(16, 512), hidden=hidden, rnn=rnn, mean_degree=4.0)
+    seq = synth.make_sequence(wl)
+    params, tgt = torch.from_numpy(synth.make_params(wl, bias_scale=0.2)).cuda(), torch.from_numpy(synth.make_target(wl)).cuda()
+
+    def run(arena, timed=False):
+        ctx = reinc.Context.for_workload(wl, arena_bytes=arena)
+        try:
+            ctx.load_sequence(seq)
+            grads = torch.full_like(params, 7.0)
+            ctx.forward_window(0, length, params, tgt, torch.zeros(1, device="cuda"))
+            if timed:
+                ctx.profile_begin(["elem", "gemm_rows"])
+            ctx.backward_window(0, length, params, tgt, grads)
+            seen = {k: v[0] for k, v in ctx.profile_end().items()} if timed else {}
+            torch.cuda.synchronize()
+            return grads, seen
+        except reinc.ReincError:
+            return None, {}
+        finally:
+            ctx.close()
+
+    roomy, _ = run(1 << 26)
+    low, high = 1 << 18, 1 << 26  # the smallest arena that the pass takes: no room for either
+    while high - low > 4096:
+        mid = (low + high) // 2 & ~255
+        low, high = (low, mid) if run(mid)[0] is not None else (mid, high)
+    tight = high + (64 << 10)  # W_h^T takes 48 KiB (GRU) or 64 KiB at most, W_i^T 384 KiB or more, a second timestep 380 KiB
+    tight += (16 << 10) if rnn == "lstm" else 0
+    plain, _ = run(tight)
+    counted, seen = run(tight, True)
+    assert seen["elem"] == length and seen["gemm_rows"] == length, seen  # (W_i^T's, one per batch of one timestep)
+    for grads in (plain, counted):
+        assert_close(grads.cpu().numpy(), roomy.cpu().numpy(), RTOL_FP32, "gradients")
