@@ -570,3 +570,49 @@ def test_backward_with_room_for_the_recurrent_weights_alone(rnn):
     assert seen["elem"] == length and seen["gemm_rows"] == length, seen  # (W_i^T's, one per batch of one timestep)
     for grads in (plain, counted):
         assert_close(grads.cpu().numpy(), roomy.cpu().numpy(), RTOL_FP32, "gradients")
+
+
+# The backward recurrence is as close to 64 bits as the product of a gate gradient's row with W_i^T by itself (timed passes
+# launch it apart), and rows that share a block with wide ones are as close as among their like.  Nodes without edges whose
+# features are the unit vectors: layer 1's weight gradient holds the rows of the input's gradient.
+@pytest.mark.parametrize("rnn,hidden", [("gru", 8), ("gru", 16), ("gru", 24), ("gru", 32), ("gru", 40), ("gru", 64), ("gru", 128),
+                                        ("lstm", 8), ("lstm", 16), ("lstm", 24), ("lstm", 32), ("lstm", 64), ("lstm", 128)])
+def test_backward_products_are_as_close_as_those_of_a_launch_each(rnn, hidden):
+    import torch
+
+    from helpers import oracle_feats, oracle_graphs
+    from paper_2501_15348_amd import reinc, synth
+
+    n = 256
+    wl = synth.WORKLOADS["c3"].scaled(n, 1, dims=(n, 100), hidden=hidden, rnn=rnn, agg="sum", feat_dtype="fp32", mean_degree=4.0)
+    seq = synth.make_sequence(wl)
+    seq.edges[0] = (np.zeros(0, dtype=np.int32), np.zeros(0, dtype=np.int32))
+    seq.x0 = np.eye(n, dtype=np.float32)
+    flat = synth.make_params(wl)
+    synth.split_params(wl, flat)["b1"][:] = 1.0  # (every unit of layer 1 is on)
+    normal = synth.make_target(wl)
+    huge = normal.copy()
+    huge[::32, 0] *= 1e19  # the row's other elements are below 2^-60 of it
+    ctx = reinc.Context.for_workload(wl, arena_bytes=1 << 26)
+    ctx.load_sequence(seq)
+    params = torch.from_numpy(flat).cuda()
+    rest = np.arange(n) % 32 != 0
+
+    def error(target, timed):
+        tgt, grads = torch.from_numpy(target).cuda(), torch.empty_like(params)
+        ctx.forward_window(0, 1, params, tgt, torch.zeros(1, device="cuda"))
+        if timed:
+            ctx.profile_begin(["elem"])
+        ctx.backward_window(0, 1, params, tgt, grads)
+        if timed:
+            ctx.profile_end()
+        q = synth.split_params(wl, flat.astype(np.float64))
+        _, ref_h, saved = oracle.forward_window(oracle_graphs(seq), [oracle_feats(seq, 0)], q, 1, "sum", True, rnn, target.astype(np.float64), keep=True)
+        ref = oracle.backward_window(oracle_graphs(seq), saved, ref_h, q, 1, "sum", True, rnn, target.astype(np.float64))["W1"][rest]
+        got = synth.split_params(wl, grads.cpu().numpy().astype(np.float64))["W1"][rest]
+        return np.linalg.norm(got - ref) / np.linalg.norm(ref)
+
+    apart, together, beside_wide = error(normal, True), error(normal, False), error(huge, False)
+    ctx.close()
+    assert together <= 1.005 * apart, (together, apart)  # (the rms of 24 000 rounded values is known to about 0.5 %)
+    assert beside_wide <= 1.05 * together, (beside_wide, together)
