@@ -468,6 +468,8 @@ struct RnnBackward {
 bool rnn_backward_exact(int lstm, int32_t H);
 // whether the launch takes this width, without and with dz: asked before the gate gradients are laid out its way
 bool rnn_backward_planes_ready(int lstm, int32_t H, bool input);
+// whether the product with W_i^T is for launch_gemm_rows, over `rows` rows of all timesteps
+bool rnn_backward_input_apart(int lstm, int32_t H, int64_t rows, int32_t d);
 bool launch_rnn_backward_planes(const PlaneJob *wh, const PlaneJob *wi, int lstm, const RnnBackward &b, hipStream_t s);
 uint64_t reduce_partial_bytes(int64_t n, int32_t K, int32_t M);
 // partial[chunk] (+)= (row_scale .* A)^T G over the chunk's rows, with the column sums of G in row K; `accumulate`

@@ -842,7 +842,7 @@ int reinc_backward_window(reinc_ctx *ctx, int32_t t0, int32_t L, const float *pa
     // ... and with the input's gradient, unless one of the kinds of work that this launch does is being timed: then the
     // steps and the product with W_i^T are launched apart
     const bool timed = ctx->prof_mask & (1u << REINC_K_ELEM | 1u << REINC_K_GEMM_ROWS);
-    const bool input = chain && !timed && (exact || plane_wiT >= 0) && rnn_backward_planes_ready(lstm, H, true);
+    const bool input_ready = chain && !timed && (exact || plane_wiT >= 0) && rnn_backward_planes_ready(lstm, H, true);
     const int ldg = chain ? 4 * H : KH;
     float *dgi = f32(uint64_t(rowsB) * ldg);
     float *dgh = lstm || chain ? dgi : f32(uint64_t(rowsB) * ldg);
@@ -885,6 +885,7 @@ int reinc_backward_window(reinc_ctx *ctx, int32_t t0, int32_t L, const float *pa
         const int32_t lo = std::max(0, hi - B + 1);
         const int nb = hi - lo + 1;
         const int dl = c.dims[Lg];
+        const bool input = input_ready && !rnn_backward_input_apart(lstm, H, int64_t(nb) * nt, dl);
         // the recurrent chain of the batch, last timestep first
         const int each = timed ? 1 : nb;  // timesteps of a launch
         for (int32_t i = hi; i >= lo && chain; i -= each) {

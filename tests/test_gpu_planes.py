@@ -616,3 +616,28 @@ def test_backward_products_are_as_close_as_those_of_a_launch_each(rnn, hidden):
     ctx.close()
     assert together <= 1.005 * apart, (together, apart)  # (the rms of 24 000 rounded values is known to about 0.5 %)
     assert beside_wide <= 1.05 * together, (beside_wide, together)
+
+
+# The widest cells whose product with W_i^T keeps three bf16 planes over many rows: by itself, timed or not, from the same
+# gate gradients.
+@pytest.mark.parametrize("rnn,hidden", [("gru", 32), ("lstm", 16)])
+def test_input_gradient_of_few_terms_keeps_its_product(rnn, hidden):
+    import torch
+
+    from paper_2501_15348_amd import reinc, synth
+
+    length, n = 8, 8193
+    wl = synth.WORKLOADS["c3"].scaled(n, length, dims=(16, 40), hidden=hidden, rnn=rnn, mean_degree=2.0)
+    ctx = reinc.Context.for_workload(wl, arena_bytes=1 << 28)
+    ctx.load_sequence(synth.make_sequence(wl))
+    params, tgt = torch.from_numpy(synth.make_params(wl, bias_scale=0.2)).cuda(), torch.from_numpy(synth.make_target(wl)).cuda()
+    ctx.forward_window(0, length, params, tgt, torch.zeros(1, device="cuda"))
+    grads = []
+    for timed in (False, True):
+        grads.append(torch.empty_like(params))
+        if timed:
+            ctx.profile_begin(["elem", "gemm_rows"])
+        ctx.backward_window(0, length, params, tgt, grads[-1])
+    assert ctx.profile_end()["gemm_rows"][0] == 1  # (all timesteps at once)
+    assert torch.equal(grads[0], grads[1])
+    ctx.close()
