@@ -463,9 +463,9 @@ def test_window_weights_are_out_of_the_arenas_way(model, rnn, hidden, n):
     ctx.close()
 
 
-# one profiled launch per timestep of the backward recurrence, whether gate gradients and product share it (64 units, but
+# one profiled launch per timestep of the backward recurrence, whether gate gradients and product share it (64 and 16 units, but
 # for the first timestep) or the width is not for that kernel (136, 44)
-@pytest.mark.parametrize("hidden,products", [(64, 0), (136, 2), (44, 2)])
+@pytest.mark.parametrize("hidden,products", [(64, 0), (16, 0), (136, 2), (44, 2)])
 def test_profile_counts_launches_of_the_backward_recurrence_once(hidden, products):
     import torch
 
