@@ -807,17 +807,18 @@ int reinc_backward_window(reinc_ctx *ctx, int32_t t0, int32_t L, const float *pa
     if (c.agg_kind != REINC_AGG_SUM)
         for (int l = 1; l <= Lg; ++l)
             if (ctx->rows_of_layer(l) < n && !transform_first(c, l)) scale_rows = std::max(scale_rows, ctx->rows_of_layer(l));
+    // all steps of a batch back in time in one launch, which keeps a GRU's gate gradients as one array of 4 H columns
+    // (otherwise 3 H twice), if the planes of W_h^T find room
+    bool chain = rnn_backward_planes_ready(lstm, H, false);
+    const bool exact = rnn_backward_exact(lstm, H);  // (no planes needed)
     auto batch_bytes = [&](int B) {
         const uint64_t rows = uint64_t(B) * uint64_t(n);
         uint64_t b = align256(uint64_t(B) * uint64_t(scale_rows) * 4);
-        b += align256(rows * KH * 4) * (lstm ? 1 : 2) + 3 * align256(rows * maxd * 4);  // (a GRU's 4 H floats once, or 3 H twice)
+        b += (lstm || chain ? align256(rows * 4 * H * 4) : 2 * align256(rows * KH * 4)) + 3 * align256(rows * maxd * 4);
         b += align256(reduce_partial_bytes(int64_t(rows), c.dims[Lg], KH)) + align256(reduce_partial_bytes(int64_t(rows), H, KH));
         for (int l = 1; l <= Lg; ++l) b += align256(reduce_partial_bytes(int64_t(rows), c.dims[l - 1], c.dims[l]));
         return b + align256(column_sums_bytes(maxd));
     };
-    // all steps of a batch back in time in one launch, which keeps a GRU's gate gradients as one array of 4 H columns
-    bool chain = rnn_backward_planes_ready(lstm, H, false);
-    const bool exact = rnn_backward_exact(lstm, H);  // (no planes needed)
     // the transposed weights come before the depth of a batch, but not before a batch of one timestep
     Planes planes;
     int plane_whT = -1, plane_wiT = -1, plane_wT[REINC_MAX_GCN_LAYERS + 1] = {-1, -1, -1, -1};
@@ -1125,9 +1126,10 @@ int reinc_backward_window_integrated(reinc_ctx *ctx, int32_t t0, int32_t L, cons
     float *dh = f32(uint64_t(n) * H), *dh2 = f32(uint64_t(n) * H), *dah = f32(uint64_t(n) * H);
     float *dc = lstm ? f32(uint64_t(n) * H) : nullptr, *dc2 = lstm ? f32(uint64_t(n) * H) : nullptr;
     bool ok = dh && dh2 && dah && (!lstm || (dc && dc2));
+    bool fused = rnn_backward_planes_ready(lstm, H, false);  // (see reinc_backward_window)
     auto batch_bytes = [&](int B) {
         const uint64_t rows = uint64_t(B) * uint64_t(n);
-        return align256(rows * KH * 4) * (lstm ? 1 : 2) + align256(reduce_partial_bytes(int64_t(rows), d0, KH)) +
+        return (lstm || fused ? align256(rows * 4 * H * 4) : 2 * align256(rows * KH * 4)) + align256(reduce_partial_bytes(int64_t(rows), d0, KH)) +
                align256(reduce_partial_bytes(int64_t(rows), H, KH));
     };
     // the transposed weights come before the depth of a batch, but not before a batch of one timestep
@@ -1135,6 +1137,7 @@ int reinc_backward_window_integrated(reinc_ctx *ctx, int32_t t0, int32_t L, cons
     int plane_whT = -1;
     if (const uint64_t bytes = planes_bytes(KH, 0, 1, H); ok && Planes::wanted(KH, 0, H) && batch_bytes(1) + align256(bytes) <= ctx->top - ctx->bottom)
         plane_whT = planes.add(ctx->scratch(bytes), W_h, nullptr, KH, 0, KH, 1, 1, H);
+    fused = fused && (rnn_backward_exact(lstm, H) || plane_whT >= 0);
     const uint64_t free_bytes = ok ? ctx->top - ctx->bottom : 0;
     int B = std::min<int>(L, ctx->max_batch);
     while (B > 1 && batch_bytes(B) > free_bytes) --B;
@@ -1143,7 +1146,6 @@ int reinc_backward_window_integrated(reinc_ctx *ctx, int32_t t0, int32_t L, cons
         return ctx->fail(REINC_E_NOMEM, "arena exhausted: no room for the backward scratch buffers");
     }
     const int64_t rowsB = int64_t(B) * n;
-    const bool fused = rnn_backward_planes_ready(lstm, H, false) && (rnn_backward_exact(lstm, H) || plane_whT >= 0);  // (see reinc_backward_window)
     const int ldg = fused ? 4 * H : KH, gap_at = fused && !lstm ? 2 * H : INT_MAX;
     float *dgi = f32(uint64_t(rowsB) * ldg);
     float *dgh = lstm || fused ? dgi : f32(uint64_t(rowsB) * ldg);

@@ -641,3 +641,40 @@ def test_input_gradient_of_few_terms_keeps_its_product(rnn, hidden):
     assert ctx.profile_end()["gemm_rows"][0] == 1  # (all timesteps at once)
     assert torch.equal(grads[0], grads[1])
     ctx.close()
+
+
+# A GRU's gate gradients take 4 H floats a row: so many more timesteps of a window fit the arena at once (the product with
+# W_i^T is launched once per batch of timesteps).
+def test_batch_of_timesteps_counts_the_gate_gradients_once():
+    import torch
+
+    from paper_2501_15348_amd import reinc, synth
+
+    n, hidden, length = 20000, 64, 4
+    wl = synth.WORKLOADS["c3"].scaled(n, length, dims=(16, 16), hidden=hidden, rnn="gru", mean_degree=2.0)
+    seq = synth.make_sequence(wl)
+    params, tgt = torch.from_numpy(synth.make_params(wl)).cuda(), torch.from_numpy(synth.make_target(wl)).cuda()
+
+    def batches(mib):
+        ctx = reinc.Context.for_workload(wl, arena_bytes=mib << 20)
+        try:
+            ctx.load_sequence(seq)
+            ctx.forward_window(0, length, params, tgt, torch.zeros(1, device="cuda"))
+            ctx.profile_begin(["gemm_rows"])
+            ctx.backward_window(0, length, params, tgt, torch.empty_like(params))
+            return ctx.profile_end()["gemm_rows"][0]
+        except reinc.ReincError:
+            return length + 1
+        finally:
+            ctx.close()
+
+    def smallest(most):  # the smallest arena that needs at most so many batches, in MiB
+        low, high = 16, 1024
+        while high - low > 1:
+            mid = (low + high) // 2
+            low, high = (low, mid) if batches(mid) <= most else (mid, high)
+        return high
+
+    grown = smallest(1) - smallest(length)  # three timesteps more: gate gradients, three arrays of layer gradients ...
+    partials = 3 * n // 256 * (16 + 16 + 1 + hidden + 1) * 3 * hidden * 4  # ... and at most the weight gradients' partial sums
+    assert grown <= (3 * n * (4 * hidden + 3 * hidden) * 4 + partials) / 2**20 + 2, grown
