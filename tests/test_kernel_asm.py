@@ -152,3 +152,18 @@ def test_packed_lstm_cell_keeps_its_loads_in_flight_and_its_epilogue_short(assem
     assert waits and min(waits) >= 10, sorted(set(waits))
     selects = sum(t.startswith("v_cndmask") for b in steady for t, _ in blocks[b])
     assert selects <= 600, selects
+
+
+def test_rows_past_the_last_are_cut_off_by_the_checked_offset(tmp_path):
+    """The backward recurrence leaves its last row tile's missing rows to the range check of the buffer instructions, which
+    covers the vector offset on every target; a row's offset in the scalar operand need not be checked."""
+    if not os.path.exists(HIPCC):
+        pytest.skip("no hipcc")
+    src = os.path.join(os.path.dirname(SRC), "kernels_planes.hip")
+    out = tmp_path / "kernels_planes.ll"  # (as the front end leaves it: optimised, the file takes two minutes)
+    subprocess.run([HIPCC, "--offload-arch=gfx950", "-O1", "-std=c++17", "-Wno-unused-function", "-I", os.path.join(ROOT, "include"), "-I",
+                    os.path.dirname(SRC), "--cuda-device-only", "-Xclang", "-disable-llvm-passes", "-emit-llvm", "-S", src, "-o", str(out)],
+                   check=True, capture_output=True)
+    found = re.findall(r"call \S+ @llvm\.amdgcn\.raw\.ptr\.buffer\.(?:load|store)[^(]*\(([^\n]*)\)", out.read_text())
+    assert len(found) >= 6, "the masked tiles were not found: have the kernels changed?"
+    assert all(re.search(r"ptr addrspace\(8\) [^,]+, i32 (%\S+), i32 0, i32 (immarg )?0$", args) for args in found), found[:4]
