@@ -81,13 +81,21 @@ __device__ inline void store_f32(float *base, int64_t row, int d, int li, const 
         *reinterpret_cast<float4 *>(base + row * d + li * VEC + i) = make_float4(r[i], r[i + 1], r[i + 2], r[i + 3]);
 }
 
+// Rows in flight per lane group of a long row's wave: as for short rows, but fewer where the kernel, which holds both paths,
+// would take more than 64 registers and leave the short rows seven or six wavefronts per SIMD in place of eight.  With
+// kSumUnroll -> this, mean degree 20: 1.5e6 rows of 256 bf16 values 2855 -> 2626 us, of 64 927 -> 838, of 32 fp32 values 519 ->
+// 475; the price, where long rows are the tail: 1e5 rows, mean degree 10, of 256 bf16 values 88 -> 90, of 32 fp32 values 20 -> 21.
+// (Bounding the kernel to eight wavefronts instead spills: 2661, 878; 1e5 rows 92, 23.)
+template <int LPR, bool BF16>
+constexpr int kLongUnroll = BF16 ? (LPR >= 4 && LPR <= 32 ? 2 : 4) : LPR == 8 ? 6 : kSumUnroll<false>;
+
 // Sums in_scale[u] * X[u] over the entries [beg, end) handled by this wave (entry e goes to lane group e % G).
 template <int LPR, bool BF16>
 __device__ inline void gather_segment(const int32_t *idx, int64_t beg, int64_t end, int64_t stride, const void *X,
                                       const float *in_scale, int32_t src_limit, int d, int lane, float (&acc)[Row<BF16>::kVec])
 {
     constexpr int VEC = Row<BF16>::kVec;
-    constexpr int G = 64 / LPR;
+    constexpr int G = 64 / LPR, U = kLongUnroll<LPR, BF16>;
     const int g = lane / LPR, li = lane % LPR;
     for (int64_t base = beg; base < end; base += stride) {
         const int cnt = int(min(int64_t(64), end - base));
@@ -98,12 +106,12 @@ __device__ inline void gather_segment(const int32_t *idx, int64_t beg, int64_t e
             if (in_scale) my_sc = in_scale[my_u];
             if (my_u >= src_limit) my_u = -1;
         }
-        for (int k = 0; k < cnt; k += G * kSumUnroll<BF16>) {
-            float r[kSumUnroll<BF16>][VEC];
-            float sc[kSumUnroll<BF16>];
+        for (int k = 0; k < cnt; k += G * U) {
+            float r[U][VEC];
+            float sc[U];
             // the row gathers depend only on the column ids: issue them before touching the gathered scales
 #pragma unroll
-            for (int j = 0; j < kSumUnroll<BF16>; ++j) {
+            for (int j = 0; j < U; ++j) {
                 const int e = k + j * G + g;
                 const int32_t u = __shfl(my_u, e & 63);
                 if (e < cnt && u >= 0) {
@@ -114,13 +122,13 @@ __device__ inline void gather_segment(const int32_t *idx, int64_t beg, int64_t e
                 }
             }
 #pragma unroll
-            for (int j = 0; j < kSumUnroll<BF16>; ++j) {
+            for (int j = 0; j < U; ++j) {
                 const int e = k + j * G + g;
                 sc[j] = __shfl(my_sc, e & 63);
                 if (e >= cnt) sc[j] = 0.0f;
             }
 #pragma unroll
-            for (int j = 0; j < kSumUnroll<BF16>; ++j)
+            for (int j = 0; j < U; ++j)
 #pragma unroll
                 for (int i = 0; i < VEC; ++i) acc[i] += sc[j] * r[j][i];
         }

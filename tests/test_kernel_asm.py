@@ -167,3 +167,20 @@ def test_rows_past_the_last_are_cut_off_by_the_checked_offset(tmp_path):
     found = re.findall(r"call \S+ @llvm\.amdgcn\.raw\.ptr\.buffer\.(?:load|store)[^(]*\(([^\n]*)\)", out.read_text())
     assert len(found) >= 6, "the masked tiles were not found: have the kernels changed?"
     assert all(re.search(r"ptr addrspace\(8\) [^,]+, i32 (%\S+), i32 0, i32 (immarg )?0$", args) for args in found), found[:4]
+
+
+def test_gathers_leave_room_for_eight_wavefronts(tmp_path):
+    """The gather kernel holds the paths of long and of short rows.  Of its 512 vector registers a SIMD gives eight wavefronts 64
+    each; rows that come from memory pay for every wavefront less (1.5e6 rows of 64 bf16 values, 66 registers: 11 %)."""
+    if not os.path.exists(HIPCC):
+        pytest.skip("no hipcc")
+    src = os.path.join(os.path.dirname(SRC), "kernels_agg.hip")
+    out = tmp_path / "kernels_agg.s"
+    subprocess.run([HIPCC, "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wno-unused-function", "-Xclang", "-target-feature",
+                    "-Xclang", "-packed-fp32-ops", "-I", os.path.join(ROOT, "include"), "-I", os.path.dirname(SRC), "--cuda-device-only",
+                    "-S", src, "-o", str(out)], check=True, capture_output=True)
+    kernels = re.findall(r"\.name:\s+(\S*aggregate_rowsILi\d+ELb[01]E\S*)(.*?)\.wavefront_size", out.read_text(), re.S)
+    assert len(kernels) == 14, [k for k, _ in kernels]
+    for name, notes in kernels:
+        vgprs, spilled = (int(re.search(rf"\.{key}:\s+(\d+)", notes).group(1)) for key in ("vgpr_count", "vgpr_spill_count"))
+        assert vgprs <= 64 and spilled == 0, (name, vgprs, spilled)
