@@ -741,8 +741,9 @@ int reinc_forward_window(reinc_ctx *ctx, int32_t t0, int32_t L, const float *par
                                    return REINC_OK;
                                }));
         }
-        // all timesteps of the batch in one launch; one by one while recurrent steps are being timed
-        if (const PlaneJob *w = planes.get(plane_rnn); w && hi > lo && !(ctx->prof_mask & (1u << REINC_K_RNN))) {
+        // all timesteps of the batch in one launch; one by one where that is faster and while recurrent steps are being timed
+        if (const PlaneJob *w = planes.get(plane_rnn);
+            w && hi > lo && rnn_chain_pays(lstm, nt, c.dims[Lg], H) && !(ctx->prof_mask & (1u << REINC_K_RNN))) {
             LocalStep &st = ctx->local[lo];
             const LocalStep *pv = lo ? &ctx->local[lo - 1] : nullptr;
             const float *hp = pv ? (const float *)pv->h : nof;
