@@ -184,3 +184,14 @@ def test_gathers_leave_room_for_eight_wavefronts(tmp_path):
     for name, notes in kernels:
         vgprs, spilled = (int(re.search(rf"\.{key}:\s+(\d+)", notes).group(1)) for key in ("vgpr_count", "vgpr_spill_count"))
         assert vgprs <= 64 and spilled == 0, (name, vgprs, spilled)
+
+
+@pytest.mark.parametrize("name", ["kernels_agg", "kernels_dense", "kernels_planes", "kernels_small"])
+def test_wide_loads_state_their_alignment(name):
+    """A wide load from an address that is only a float's (weight matrices follow one another) goes through a type that says so."""
+    if not os.path.exists(HIPCC):
+        pytest.skip("no hipcc")
+    src = os.path.join(os.path.dirname(SRC), name + ".hip")
+    run = subprocess.run([HIPCC, "--offload-arch=gfx950", "-std=c++17", "-I", os.path.join(ROOT, "include"), "-I", os.path.dirname(SRC),
+                          "--cuda-device-only", "-fsyntax-only", "-Werror=align-mismatch", src], capture_output=True, text=True)
+    assert run.returncode == 0, run.stderr[-2000:]
