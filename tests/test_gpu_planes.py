@@ -678,3 +678,73 @@ def test_batch_of_timesteps_counts_the_gate_gradients_once():
     grown = smallest(1) - smallest(length)  # three timesteps more: gate gradients, three arrays of layer gradients ...
     partials = 3 * n // 256 * (16 + 16 + 1 + hidden + 1) * 3 * hidden * 4  # ... and at most the weight gradients' partial sums
     assert grown <= (3 * n * (4 * hidden + 3 * hidden) * 4 + partials) / 2**20 + 2, grown
+
+
+# The rare branches of a window's recurrent launches: weights with elements far below the others of their row (wide columns of
+# W_h^T and W_i^T, and of the forward weights), input rows with three and with twelve elements far below the row's largest one
+# (which meets no weight, so that the others decide), states with elements near 2^-40.  Forward bitwise against a launch per
+# step, everything against 64 bits.
+@pytest.mark.parametrize("rnn", ["gru", "lstm"])
+@pytest.mark.parametrize("hidden", [40, 64, 128])
+@pytest.mark.parametrize("case", ["columns", "listed", "wide", "state"])
+def test_unequal_magnitudes_in_the_steps_of_a_window(rnn, hidden, case):
+    import torch
+
+    from helpers import oracle_feats, oracle_graphs
+    from paper_2501_15348_amd import reinc, synth
+
+    n, top, length = 833, 48, 4
+    wl = synth.WORKLOADS["c3"].scaled(n, length, dims=(16, top), hidden=hidden, rnn=rnn, mean_degree=4.0)
+    seq = synth.make_sequence(wl)
+    ctx = reinc.Context.for_workload(wl, arena_bytes=1 << 27)
+    ctx.load_sequence(seq)
+    ctx.build_deltas(-1)
+    flat, target = synth.make_params(wl, bias_scale=0.2), synth.make_target(wl)
+    p = synth.split_params(wl, flat)  # (views)
+    p["b1"][:] = np.abs(p["b1"]) + 0.1
+    groups = [np.arange(top)]  # columns of layer 1 of like magnitude
+    if case == "columns":
+        for name, row in (("W_h", 3), ("W_h", hidden - 1), ("W_i", 5), ("W_i", top - 1)):
+            p[name][row, 2::7] *= np.float32(2.0**-40)
+    elif case == "state":
+        unit = 2 * hidden + np.array([1, 7, hidden - 2])  # the candidate gate's columns of three units
+        for name in ("W_i", "W_h", "b_i", "b_h"):
+            p[name][..., unit] *= np.float32(2.0**-40)
+    else:
+        few = np.arange(1, 4 if case == "listed" else 13)
+        rest = np.arange(few[-1] + 1, top)
+        for cols, up in ((np.array([0]), 36), (rest, 20)):
+            p["W1"][:, cols] *= np.float32(2.0**up)
+            p["b1"][cols] *= np.float32(2.0**up)
+        p["W_i"][0] = 0.0
+        p["W_i"][rest] *= np.float32(2.0**-20)
+        groups = [few, rest]
+    params, tgt = torch.from_numpy(flat).cuda(), torch.from_numpy(target).cuda()
+
+    def run(timed):
+        out = [torch.zeros(1, device="cuda"), torch.full((n, hidden), 7.0, device="cuda"), torch.empty_like(params)]
+        if timed:
+            ctx.profile_begin(["rnn", "elem", "gemm_rows"])
+        ctx.forward_window(0, length, params, tgt, out[0], out[1])
+        ctx.backward_window(0, length, params, tgt, out[2])
+        if timed:
+            ctx.profile_end()
+        torch.cuda.synchronize()
+        return out
+
+    one, apart = run(False), run(True)
+    ctx.close()
+    assert torch.equal(one[0], apart[0]) and torch.equal(one[1], apart[1])
+    q = synth.split_params(wl, flat.astype(np.float64))
+    graphs, feats = oracle_graphs(seq), [oracle_feats(seq, t) for t in range(length)]
+    _, ref_h, saved = oracle.forward_window(graphs, feats, q, 1, wl.agg, wl.self_loop, rnn, target, keep=True)
+    ref = oracle.backward_window(graphs, saved, ref_h, q, 1, wl.agg, wl.self_loop, rnn, target)
+    assert_close(one[1].cpu().numpy(), ref_h, RTOL_FP32, "h_last")
+    for what, grads in (("together", one[2]), ("apart", apart[2])):
+        got = synth.split_params(wl, grads.cpu().numpy())
+        for name in ("W_h", "b_i", "b_h"):
+            assert_close(got[name], ref[name], RTOL_FP32, f"{name}, {what}")
+        for cols in groups:
+            assert_close(got["W_i"][cols], ref["W_i"][cols], RTOL_FP32, f"W_i, {what}")
+            # (a unit of layer 1 near zero may be on in one and off in the other: a few entries of the sums over all rows)
+            assert_close(got["W1"][:, cols], ref["W1"][:, cols], 1e-3, f"W1, {what}")
