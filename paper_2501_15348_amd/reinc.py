@@ -174,6 +174,10 @@ def _stream():
     """Handle of the current stream of the current device.  (torch.cuda.current_stream() makes an object of it first: 3.0 us of
     the 10.5 that a small gcn_transform took on the host; this 0.2.)"""
     c = _torch_c()
+    if c._cuda_isInBadFork():  # a process forked from one that had initialised the GPU: torch's own error
+        import torch
+
+        torch.cuda.init()
     return c._cuda_getCurrentRawStream(c._cuda_getDevice())
 
 

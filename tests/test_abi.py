@@ -53,3 +53,24 @@ def test_bad_config_reports_text(lib):
     assert rc == reinc.E_ARG and h.value
     assert b"num_nodes" in lib.reinc_last_error(h)
     lib.reinc_destroy(h)
+
+
+def test_a_forked_process_is_refused_as_by_torch(monkeypatch):
+    """The binding asks torch for the raw stream; in a process forked after the GPU was initialised it raises torch's error
+    instead of handing on the parent's handles."""
+    import torch
+
+    from paper_2501_15348_amd import reinc
+
+    class Forked:
+        _cuda_isInBadFork = staticmethod(lambda: True)
+        _cuda_getDevice = staticmethod(lambda: 0)
+        _cuda_getCurrentRawStream = staticmethod(lambda device: 0)
+
+    def refuse():
+        raise RuntimeError("Cannot re-initialize CUDA in forked subprocess")
+
+    monkeypatch.setattr(reinc, "_torch_c", lambda: Forked)
+    monkeypatch.setattr(torch.cuda, "init", refuse)
+    with pytest.raises(RuntimeError, match="forked"):
+        reinc._stream()
