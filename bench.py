@@ -342,7 +342,7 @@ def extras(ctx, wl, seq, infos, params, target, step, step_s, full):
     full_rate = fb * len(full_ms) / (sum(full_ms) * 1e-3) / 1e9
     res["aggregate_full"] = {"mean_us": round(1e3 * sum(full_ms) / len(full_ms), 2), "algorithmic_GBps": round(full_rate, 1),
                              "hbm_frac": round(full_rate / HBM_PEAK_GBS, 4),
-                             "note": "both kernels of a from-scratch aggregation (rows of up to 64 entries, hub rows)"}
+                             "note": "one launch: a block per hub row, a group of lanes per row of up to 64 entries"}
     if full_rate > HBM_PEAK_GBS:
         res["aggregate_full"]["note"] += "; cache-served: above the HBM peak because gathered rows are re-used out of the caches"
     res["incremental_speedup_over_full"] = round(sum(full_ms) / sum(ip_ms), 3)
