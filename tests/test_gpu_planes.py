@@ -66,6 +66,25 @@ def test_row_product_of_many_rows(ctx, n, k, m):
     assert bool(((out - ref).abs() <= _bound(a.double(), w.double())).all())
 
 
+# from where the prepared form is taken of 65 to 127 columns and of 96 terms: first and ragged row counts, the first and the
+# last of those columns, numbers of k-steps that leave the ring of four early or not
+@pytest.mark.parametrize("n,k,m", [(16384, 224, 65), (16385, 256, 127), (16447, 320, 97), (16384, 416, 80), (98304, 96, 129)])
+@pytest.mark.parametrize("bf16", [False, True])
+def test_row_product_where_it_begins_to_pay(ctx, n, k, m, bf16):
+    import torch
+
+    first = 16384 if m < 128 else 98304
+    assert _prepared(n, k, m) and not _prepared(first - 1, k, m)
+    g = torch.Generator(device="cuda").manual_seed(n + k + m)
+    a = torch.randn(n, k, generator=g, device="cuda")
+    a = a.bfloat16() if bf16 else a
+    w = torch.randn(k, m, generator=g, device="cuda") / k**0.5
+    b = torch.randn(m, generator=g, device="cuda")
+    out = ctx.gcn_transform(a, w, b, None, relu=False).double()
+    ref = a.double() @ w.double() + b.double()
+    assert bool(((out - ref).abs() <= _bound(a.double(), w.double()) + 2.0**-23 * ref.abs()).all())
+
+
 def _bound_wide(a, w):
     """... where a row or a column spans more than the planes hold: one fp32 chain over k."""
     return _bound(a, w) + a.shape[1] * 2.0**-24 * (a.abs() @ w.abs())
