@@ -585,7 +585,7 @@ int reinc_rnn_step_work(reinc_ctx *ctx, int rnn_kind, const float *x, int64_t n,
         jobs.job[0] = plane_job(W_i, W_h, d_in, H, (lstm ? 4 : 3) * H, 0, lstm ? 4 : 3, H, work);
         launch_prepare_planes(jobs, as_stream(stream));
         if (launch_rnn_planes(jobs.job[0], lstm, x, nullptr, n, h_prev, lstm ? c_prev : h_prev, b_i, b_h, h_out, c_out, saved,
-                              as_stream(stream))) {
+                              as_stream(stream), 1, 0, 0, 0, true)) {
             REINC_HIP(ctx, hipGetLastError());
             return REINC_OK;
         }

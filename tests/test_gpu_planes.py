@@ -547,6 +547,33 @@ def test_steps_of_a_window_in_one_launch(rnn, n, hidden, top):
     ctx.close()
 
 
+# Recurrent steps gate by gate, in the launch of a window (more than one block of 64 rows a compute unit: the first row count
+# and ragged ones) and by themselves: one, two and four waves of columns, three tiles of units on four waves, input and state of
+# k-steps that leave the ring of four early or not, no state at first.
+@pytest.mark.parametrize("rnn", ["gru", "lstm"])
+@pytest.mark.parametrize("n,hidden,top", [(16385, 64, 24), (16448, 64, 96), (16411, 96, 64), (16391, 128, 31), (16447, 128, 160)])
+def test_window_gate_by_gate(rnn, n, hidden, top):
+    import torch
+
+    from helpers import oracle_feats, oracle_graphs
+    from paper_2501_15348_amd import reinc, synth
+
+    length = 3
+    wl = synth.WORKLOADS["c3"].scaled(n, length, dims=(16, top), hidden=hidden, rnn=rnn, mean_degree=2.0)
+    seq = synth.make_sequence(wl)
+    ctx = reinc.Context.for_workload(wl, arena_bytes=1 << 30)
+    ctx.load_sequence(seq)
+    ctx.build_deltas(-1)
+    flat, target = synth.make_params(wl, bias_scale=0.2), synth.make_target(wl)
+    loss, h = torch.zeros(1, device="cuda"), torch.full((n, hidden), 7.0, device="cuda")
+    ctx.forward_window(0, length, torch.from_numpy(flat).cuda(), torch.from_numpy(target).cuda(), loss, h)
+    p = synth.split_params(wl, flat.astype(np.float64))
+    graphs, feats = oracle_graphs(seq), [oracle_feats(seq, t) for t in range(length)]
+    _, ref_h, _ = oracle.forward_window(graphs, feats, p, 1, wl.agg, wl.self_loop, rnn, target, keep=True)
+    assert_close(h.cpu().numpy(), ref_h, RTOL_FP32, "h_last")
+    ctx.close()
+
+
 # A backward pass whose scratch holds the prepared W_h^T but not W_i^T keeps the steps that make gate gradients and their
 # product with W_h^T together, and multiplies with W_i as it is (a GRU's gate gradients lie 4 H apart, 3 H wide).
 @pytest.mark.parametrize("rnn", ["gru", "lstm"])
