@@ -479,8 +479,15 @@ uint64_t reduce_partial_bytes(int64_t n, int32_t K, int32_t M);
 // counts can add into one set of slabs (sized by reduce_partial_bytes(n_geom, K, M)).  launch_reduce_partials
 // (with the same n_geom) then does dW[K,M] += sum of slabs, db[M] += sum of rows K.  Column c of G lies at c, from
 // `gap_at` on `gap` columns further.
+// second: another product over the same rows, of the same sizes and strides (no row scale), in the same launch.
+struct ReduceSecond {
+    const float *A, *G;
+    float *partial;
+    int32_t gap_at;
+};
 void launch_gemm_reduce(const float *A, int32_t lda, const float *row_scale, const float *G, int32_t ldg, int64_t n,
-                        int64_t n_geom, int32_t K, int32_t M, float *partial, int accumulate, int32_t gap_at, int32_t gap, hipStream_t s);
+                        int64_t n_geom, int32_t K, int32_t M, float *partial, int accumulate, int32_t gap_at, int32_t gap, hipStream_t s,
+                        const ReduceSecond *second = nullptr);
 void launch_reduce_partials(const float *partial, int64_t n, int32_t K, int32_t M, float *dW, float *db, hipStream_t s);
 void launch_rnn_backward_elem(int lstm, int64_t n, int32_t H, const float *dh, const float *dc, const float *saved,
                               const float *h_prev, const float *c_prev, const float *c_new, float *dgi, float *dgh,

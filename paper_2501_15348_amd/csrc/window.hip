@@ -930,13 +930,25 @@ int reinc_backward_window(reinc_ctx *ctx, int32_t t0, int32_t L, const float *pa
             Ap[i] = ctx->local[i].H[Lg];
             Mp[i] = i ? ctx->local[i - 1].h : ctx->zero_state;
         }
+        // (of one width and over adjacent timesteps: one launch, which takes the gate gradients' rows out of memory once)
+        bool both = false;
+        if (dl == H)
+            REINC_TRY(for_runs(lo, hi, nt, {Strip{Ap.data(), dl}, Strip{Mp.data(), H}}, [&](int, int len) {
+                both = len == nb;
+                return REINC_OK;
+            }));
+        if (both) {
+            const ReduceSecond second{Mp[lo], dgh, part_wh, chain && !lstm ? 2 * H : INT_MAX};
+            ProfScope prof(ctx, REINC_K_REDUCE, s);
+            launch_gemm_reduce(Ap[lo], dl, nof, dgi, ldg, nt * nb, rowsT, dl, KH, part_wi, acc0, INT_MAX, H, s, &second);
+        }
         int calls = 0;
-        REINC_TRY(for_runs(lo, hi, nt, {Strip{Ap.data(), dl}}, [&](int i0, int len) {
+        if (!both) REINC_TRY(for_runs(lo, hi, nt, {Strip{Ap.data(), dl}}, [&](int i0, int len) {
             reduce(Ap[i0], dl, nof, dgi + int64_t(i0 - lo) * nt * ldg, ldg, nt * len, rowsT, dl, KH, part_wi, acc0 | (calls++ > 0));
             return REINC_OK;
         }));
         calls = 0;
-        REINC_TRY(for_runs(lo, hi, nt, {Strip{Mp.data(), H}}, [&](int i0, int len) {
+        if (!both) REINC_TRY(for_runs(lo, hi, nt, {Strip{Mp.data(), H}}, [&](int i0, int len) {
             reduce(Mp[i0], H, nof, dgh + int64_t(i0 - lo) * nt * ldg, ldg, nt * len, rowsT, H, KH, part_wh, acc0 | (calls++ > 0),
                    chain && !lstm ? 2 * H : INT_MAX);
             return REINC_OK;

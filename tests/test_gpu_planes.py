@@ -574,6 +574,35 @@ def test_window_gate_by_gate(rnn, n, hidden, top):
     ctx.close()
 
 
+# Inputs as wide as the state: the gradients of W_i and W_h come out of one launch, over one timestep, a batch of them and two
+# batches; a slab a wave, four slabs a block inside the output and over its edge, rows that end inside a trip.
+@pytest.mark.parametrize("rnn", ["gru", "lstm"])
+@pytest.mark.parametrize("n,hidden,length", [(33, 32, 3), (701, 64, 1), (701, 64, 3), (645, 96, 3), (897, 128, 3), (130, 128, 9), (70, 40, 9)])
+def test_gradients_of_both_recurrent_weights_in_one_launch(rnn, n, hidden, length):
+    import torch
+
+    from helpers import GRAD_RTOL_FP32, assert_gradients_close, oracle_feats, oracle_graphs
+    from paper_2501_15348_amd import reinc, synth
+
+    wl = synth.WORKLOADS["c3"].scaled(n, length, dims=(16, hidden), hidden=hidden, rnn=rnn, mean_degree=4.0)
+    seq = synth.make_sequence(wl)
+    ctx = reinc.Context.for_workload(wl, arena_bytes=1 << 28)
+    ctx.load_sequence(seq)
+    ctx.build_deltas(-1)
+    flat, target = synth.make_params(wl, bias_scale=0.2), synth.make_target(wl)
+    params, tgt = torch.from_numpy(flat).cuda(), torch.from_numpy(target).cuda()
+    loss, grads = torch.zeros(1, device="cuda"), torch.empty_like(params)
+    ctx.forward_window(0, length, params, tgt, loss)
+    ctx.backward_window(0, length, params, tgt, grads)
+    p = synth.split_params(wl, flat.astype(np.float64))
+    graphs, feats = oracle_graphs(seq), [oracle_feats(seq, t) for t in range(length)]
+    _, ref_h, saved = oracle.forward_window(graphs, feats, p, 1, wl.agg, wl.self_loop, rnn, target, keep=True)
+    assert_gradients_close(synth.split_params(wl, grads.cpu().numpy()), saved,
+                           lambda sv: oracle.backward_window(graphs, sv, ref_h, p, 1, wl.agg, wl.self_loop, rnn, target),
+                           [name for name, _ in synth.param_shapes(wl)], GRAD_RTOL_FP32)
+    ctx.close()
+
+
 # A backward pass whose scratch holds the prepared W_h^T but not W_i^T keeps the steps that make gate gradients and their
 # product with W_h^T together, and multiplies with W_i as it is (a GRU's gate gradients lie 4 H apart, 3 H wide).
 @pytest.mark.parametrize("rnn", ["gru", "lstm"])
