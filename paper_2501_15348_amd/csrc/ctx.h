@@ -444,10 +444,11 @@ bool launch_gemm_planes(const PlaneJob &w, const void *A, int a_bf16, int64_t n,
                         int relu, const float *add, const float *mask, float *out, hipStream_t s);
 // as launch_rnn_fused, with the weights prepared (W1 = W_i, W2 = W_h); carry: h_carry of a GRU, c_prev of an LSTM.  steps > 1:
 // so many timesteps, each with the one before's outputs as its state; a timestep later lies *_step floats further (no x_scale).
-// own_call: not a window's step (the kernel is chosen otherwise, see rnn_by_gate).
+// window: how many steps are to have one arithmetic, in whatever launches they come (the timesteps of a stacked window); 0: a
+// call of its own (see rnn_by_gate).
 bool launch_rnn_planes(const PlaneJob &w, int lstm, const float *x, const float *x_scale, int64_t n, const float *h_prev,
                        const float *carry, const float *b_i, const float *b_h, float *h_out, float *c_out, float *saved, hipStream_t s,
-                       int steps = 1, int64_t x_step = 0, int64_t state_step = 0, int64_t saved_step = 0, bool own_call = false);
+                       int steps = 1, int64_t x_step = 0, int64_t state_step = 0, int64_t saved_step = 0, int window = 1);
 // Gate gradients of `steps` recurrent steps, the latest first, with their products with W_h^T (the gradient w.r.t. the state
 // before each step) and, where dz is given, W_i^T.  Pointers are those of the latest timestep; a timestep earlier lies *_step
 // floats before.  wh, wi: the transposed weights prepared (not read where rnn_backward_exact).

@@ -76,10 +76,12 @@ void product(reinc_ctx *ctx, hipStream_t st, const PlaneJob *w, const float *A, 
 // one recurrent step; see launch_rnn_fused
 void rnn_step(reinc_ctx *ctx, hipStream_t st, const PlaneJob *w, int lstm, const float *x, const float *x_scale, int64_t n, int d_in,
               int H, const float *h_prev, const float *h_carry, const float *c_prev, const float *W_i, const float *W_h,
-              const float *b_i, const float *b_h, float *h_out, float *c_out, float *saved)
+              const float *b_i, const float *b_h, float *h_out, float *c_out, float *saved, int window = 1)
 {
     ProfScope prof(ctx, REINC_K_RNN, st);
-    if (w && launch_rnn_planes(*w, lstm, x, x_scale, n, h_prev, lstm ? c_prev : h_carry, b_i, b_h, h_out, c_out, saved, st)) return;
+    if (w && launch_rnn_planes(*w, lstm, x, x_scale, n, h_prev, lstm ? c_prev : h_carry, b_i, b_h, h_out, c_out, saved, st, 1, 0, 0, 0,
+                               window))
+        return;
     launch_rnn_fused(lstm, x, x_scale, n, d_in, H, h_prev, h_carry, c_prev, W_i, W_h, b_i, b_h, h_out, c_out, saved, st);
 }
 
@@ -585,7 +587,7 @@ int reinc_rnn_step_work(reinc_ctx *ctx, int rnn_kind, const float *x, int64_t n,
         jobs.job[0] = plane_job(W_i, W_h, d_in, H, (lstm ? 4 : 3) * H, 0, lstm ? 4 : 3, H, work);
         launch_prepare_planes(jobs, as_stream(stream));
         if (launch_rnn_planes(jobs.job[0], lstm, x, nullptr, n, h_prev, lstm ? c_prev : h_prev, b_i, b_h, h_out, c_out, saved,
-                              as_stream(stream), 1, 0, 0, 0, true)) {
+                              as_stream(stream), 1, 0, 0, 0, 0)) {
             REINC_HIP(ctx, hipGetLastError());
             return REINC_OK;
         }
@@ -748,7 +750,7 @@ int reinc_forward_window(reinc_ctx *ctx, int32_t t0, int32_t L, const float *par
             const LocalStep *pv = lo ? &ctx->local[lo - 1] : nullptr;
             const float *hp = pv ? (const float *)pv->h : nof;
             if (launch_rnn_planes(*w, lstm, st.H[Lg], nof, nt, hp, lstm && pv ? pv->c : hp, p.b_i, p.b_h, st.h, st.c, st.saved, s, hi - lo + 1,
-                                  int64_t(slice_floats(nt, c.dims[Lg])), int64_t(slice_floats(nt, H)), int64_t(slice_floats(nt, 4 * H))))
+                                  int64_t(slice_floats(nt, c.dims[Lg])), int64_t(slice_floats(nt, H)), int64_t(slice_floats(nt, 4 * H)), L))
                 continue;
         }
         for (int32_t i = lo; i <= hi; ++i) {
@@ -756,7 +758,7 @@ int reinc_forward_window(reinc_ctx *ctx, int32_t t0, int32_t L, const float *par
             const LocalStep *pv = i ? &ctx->local[i - 1] : nullptr;
             const float *hp = pv ? (const float *)pv->h : nof;
             rnn_step(ctx, s, planes.get(plane_rnn), lstm, st.H[Lg], nof, nt, c.dims[Lg], H, hp, hp, pv ? pv->c : nof, p.W_i, p.W_h,
-                     p.b_i, p.b_h, st.h, st.c, st.saved);
+                     p.b_i, p.b_h, st.h, st.c, st.saved, L);
         }
     }
     const LocalStep &last = ctx->local[L - 1];

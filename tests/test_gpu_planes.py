@@ -315,6 +315,19 @@ def test_sums_of_a_recurrent_step_are_as_close_as_with_all_gates_together(ctx, k
         assert errors[name] <= limit, (name, errors[name], limit)
 
 
+# ... and without a state, where the sums are of the input's terms alone: too few of them, and enough.
+@pytest.mark.parametrize("kind,n,d,h,limits", [
+    ("lstm", 100000, 16, 100, dict(g=1.388e-7, c=1.483e-7, h=2.888e-7)),
+    ("gru", 60000, 33, 200, dict(n=1.525e-7, h=1.598e-7)),
+    ("gru", 60000, 100, 100, dict(r=4.724e-8, z=4.769e-8, n=1.591e-7, h=1.660e-7)),
+    ("lstm", 60000, 100, 100, dict(i=4.760e-8, f=4.747e-8, g=1.569e-7, c=1.675e-7, h=3.106e-7)),
+])
+def test_sums_of_a_first_recurrent_step_are_as_close_as_with_all_gates_together(ctx, kind, n, d, h, limits):
+    errors = _step_errors(ctx, kind, n, d, h, state=False)
+    for name, limit in limits.items():
+        assert errors[name] <= limit, (name, errors[name], limit)
+
+
 # one feature of the input far above the rest over small or zero weights, an input far above the state, and a row of W_h far
 # above the rest under a zero state of that unit
 @pytest.mark.parametrize("kind", ["gru", "lstm"])
