@@ -85,6 +85,31 @@ def test_row_product_where_it_begins_to_pay(ctx, n, k, m, bf16):
     assert bool(((out - ref).abs() <= _bound(a.double(), w.double()) + 2.0**-23 * ref.abs()).all())
 
 
+# The blocks of a row product depend on its rows, terms, columns and type, its results do not: the last rows of a call of many
+# rows are those of a call by themselves, bit for bit.  Both sides of each line between the kernels, least and most of 65 to 128
+# columns and of more, ragged rows.
+@pytest.mark.parametrize("n,k,m", [(131072, 50, 65), (131073, 50, 65), (131100, 57, 128), (131073, 63, 96), (131072, 72, 97), (131073, 72, 97),
+                                   (131073, 65, 128), (131105, 95, 65), (131073, 97, 96), (16385, 193, 65), (131073, 225, 127),
+                                   (140000, 200, 128), (16384, 290, 129), (16385, 290, 129), (16417, 383, 200), (16385, 385, 160)])
+@pytest.mark.parametrize("bf16", [False, True])
+def test_row_products_do_not_depend_on_the_block(ctx, n, k, m, bf16):
+    import torch
+
+    assert _prepared(n, k, m) and _prepared(130, k, m)
+    g = torch.Generator(device="cuda").manual_seed(n + k + m)
+    a = torch.randn(n, k, generator=g, device="cuda")
+    a = a.bfloat16() if bf16 else a
+    w = torch.randn(k, m, generator=g, device="cuda") / k**0.5
+    b, rs = torch.randn(m, generator=g, device="cuda"), torch.rand(n, generator=g, device="cuda") + 0.01
+    out = ctx.gcn_transform(a, w, b, rs, relu=True)
+    for rows in (slice(0, 130), slice(n - 130, n)):
+        part = ctx.gcn_transform(a[rows].clone(), w, b, rs[rows].clone(), relu=True)
+        assert torch.equal(out[rows], part), rows
+    scaled = (a.float() * rs[:, None]).double()
+    ref = torch.relu(scaled @ w.double() + b.double())
+    assert bool(((out.double() - ref).abs() <= _bound(scaled, w.double()) + 2.0**-23 * (ref + b.double().abs())).all())
+
+
 def _bound_wide(a, w):
     """... where a row or a column spans more than the planes hold: one fp32 chain over k."""
     return _bound(a, w) + a.shape[1] * 2.0**-24 * (a.abs() @ w.abs())
