@@ -426,7 +426,7 @@ struct PlaneJobs {
     int count;
 };
 // whether the prepared form is the faster one (the measurements behind the rules stand at their definitions)
-bool planes_pay_rows(int64_t n, int K, int M);  // one product of n rows, weights prepared for it alone
+bool planes_pay_rows(int64_t n, int K, int M, bool bf16);  // one product of n rows, weights prepared for it alone
 bool planes_pay_backward(int64_t n, int K, int M);  // a backward product of the window driver, weights prepared once
 bool rnn_chain_pays(int lstm, int64_t n, int d_in, int H);  // the prepared steps of a window in one launch
 bool planes_pay_rnn(int64_t n, int d_in, int H, bool own_call);  // own_call: the weights are prepared for one step alone

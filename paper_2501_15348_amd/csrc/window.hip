@@ -507,8 +507,9 @@ extern "C" {
 
 uint64_t reinc_gcn_work_bytes(int64_t n, int32_t d_in, int32_t d_out)
 {
-    if (n <= 0 || d_in <= 0 || d_out <= 0 || !dense_split_enabled() || !planes_pay_rows(n, d_in, d_out)) return 0;
-    return planes_bytes(d_in, 0, 1, d_out);
+    if (n <= 0 || d_in <= 0 || d_out <= 0 || !dense_split_enabled()) return 0;
+    // (for either type of the rows)
+    return planes_pay_rows(n, d_in, d_out, false) || planes_pay_rows(n, d_in, d_out, true) ? planes_bytes(d_in, 0, 1, d_out) : 0;
 }
 
 int reinc_gcn_transform(reinc_ctx *ctx, const void *A, int a_dtype, int64_t n, int32_t d_in, int32_t d_out,
@@ -526,7 +527,7 @@ int reinc_gcn_transform_work(reinc_ctx *ctx, const void *A, int a_dtype, int64_t
     if (n < 0 || d_in <= 0 || d_out <= 0) return ctx->fail(REINC_E_ARG, "bad shape");
     if (a_dtype != REINC_F32 && a_dtype != REINC_BF16) return ctx->fail(REINC_E_ARG, "bad a_dtype");
     if (A == out) return ctx->fail(REINC_E_ARG, "output may not alias the input");
-    const uint64_t need = work ? reinc_gcn_work_bytes(n, d_in, d_out) : 0;
+    const uint64_t need = work && planes_pay_rows(n, d_in, d_out, a_dtype == REINC_BF16) ? reinc_gcn_work_bytes(n, d_in, d_out) : 0;
     if (need > 0 && work_bytes >= need && (reinterpret_cast<uintptr_t>(work) & 15) == 0) {
         ProfScope prof(ctx, REINC_K_GEMM_ROWS, as_stream(stream));
         PlaneJobs jobs{};

@@ -68,7 +68,7 @@ def test_row_product_of_many_rows(ctx, n, k, m):
 
 # from where the prepared form is taken of 65 to 127 columns and of 96 terms: first and ragged row counts, the first and the
 # last of those columns, numbers of k-steps that leave the ring of four early or not
-@pytest.mark.parametrize("n,k,m", [(16384, 224, 65), (16385, 256, 127), (16447, 320, 97), (16384, 416, 80), (98304, 96, 129)])
+@pytest.mark.parametrize("n,k,m", [(16384, 224, 65), (16385, 256, 127), (16447, 320, 97), (16384, 384, 80), (98304, 96, 129)])
 @pytest.mark.parametrize("bf16", [False, True])
 def test_row_product_where_it_begins_to_pay(ctx, n, k, m, bf16):
     import torch
@@ -108,6 +108,28 @@ def test_row_products_do_not_depend_on_the_block(ctx, n, k, m, bf16):
     scaled = (a.float() * rs[:, None]).double()
     ref = torch.relu(scaled @ w.double() + b.double())
     assert bool(((out.double() - ref).abs() <= _bound(scaled, w.double()) + 2.0**-23 * (ref + b.double().abs())).all())
+
+
+# The kernels with resident weights keep the shapes that they are faster at: rows that are no whole groups of eight for each of
+# eight threads, and 224 terms of bf16 rows, whose call has a work area all the same (the type is not known to its size).
+def test_row_products_that_keep_the_resident_weights(ctx):
+    import torch
+
+    from paper_2501_15348_amd import reinc
+
+    n, k, m = 16400, 224, 96
+    assert _prepared(n, k, m) and not any(_prepared(n * i, j, m) for i in (1, 3, 20) for j in (288, 352, 416))
+    g = torch.Generator(device="cuda").manual_seed(k)
+    a, w = torch.randn(n, k, generator=g, device="cuda"), torch.randn(k, m, generator=g, device="cuda") / k**0.5
+    for rows in (a, a.bfloat16()):
+        bf16 = rows.dtype == torch.bfloat16
+        resident = torch.empty(n, m, device="cuda")
+        ptr = reinc._dev_ptr
+        ctx._ck(ctx.lib.reinc_gcn_transform(ctx.handle, ptr(rows), int(bf16), n, k, m, None, ptr(w), None, 0, ptr(resident), reinc._stream()))
+        out = ctx.gcn_transform(rows, w, None, None, relu=False)
+        assert torch.equal(out, resident) == bf16
+        ref = rows.double() @ w.double()
+        assert bool(((out.double() - ref).abs() <= _bound(rows.double(), w.double())).all())
 
 
 def _bound_wide(a, w):
