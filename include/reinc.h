@@ -232,8 +232,8 @@ int reinc_rnn_step(reinc_ctx *ctx, int rnn_kind, const float *x, int64_t n, int3
 /* The same two calls with a work area for the weights in matrix-core form (they are converted on every call, nothing is
  * kept): work = device memory of at least reinc_gcn_work_bytes / reinc_rnn_work_bytes bytes, 16-byte aligned, free for
  * reuse once the call's device work is done.  Results agree with the calls above within fp32 rounding.  Where the size
- * function returns 0 (products deeper than 512, shapes that gain nothing), or with work == NULL or work_bytes too small,
- * they ARE the calls above. */
+ * function returns 0 (products deeper than 512, shapes that gain nothing), for rows of a type that gains nothing at its
+ * shape (a few shapes of bf16 rows), or with work == NULL or work_bytes too small, they ARE the calls above. */
 uint64_t reinc_gcn_work_bytes(int64_t n, int32_t d_in, int32_t d_out);
 int reinc_gcn_transform_work(reinc_ctx *ctx, const void *A, int a_dtype, int64_t n, int32_t d_in, int32_t d_out,
                              const float *row_scale, const float *W, const float *b, int relu, float *out, void *work,
