@@ -1308,10 +1308,11 @@ struct ReduceArgs {
     int accumulate;  // add to the partial slabs instead of overwriting them (later timesteps of a window)
     int gap_at, gap; // column c of G lies at c, from gap_at on `gap` columns further
     // A second product over the same rows and of the same sizes (jobs = 2), without a row scale: the gradients of W_i and W_h,
-    // whose blocks of a row chunk go to one XCD.  What it saves is a launch and its tail, of small calls above all (in turn, three
-    // times: an epoch on 1000 rows x 16 206 -> 194 us, node batches of 1562 rows 3.81 -> 3.77 ms, epochs with 1.2e6 x 128 -> 512
-    // 18.14 -> 17.99 ms, with 1.6e6 x 128 -> 384 29.56 -> 29.50, less than the runs differ).  Sums and their order are those of two
-    // launches.
+    // whose blocks of a row chunk go to one XCD and read its gate gradients together.  What it saves is a launch and its tail, of
+    // small calls above all, and bytes of large ones, which the products and splits bound as much (8e6 rows x 128 -> 512: 38.9 GB by
+    // the counters in place of 51.0, 10.8 ms in place of 11.4).  In turn, three times: an epoch on 1000 rows x 16 206 -> 194 us, node
+    // batches of 1562 rows 3.81 -> 3.77 ms, epochs with 1.2e6 x 128 -> 512 18.14 -> 17.99 ms, with 1.6e6 x 128 -> 384 29.56 -> 29.50,
+    // less than the runs differ.  Sums and their order are those of two launches.
     int jobs;
     const float *A2, *G2;
     float *partial2;

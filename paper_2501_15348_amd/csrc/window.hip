@@ -933,7 +933,7 @@ int reinc_backward_window(reinc_ctx *ctx, int32_t t0, int32_t L, const float *pa
             Ap[i] = ctx->local[i].H[Lg];
             Mp[i] = i ? ctx->local[i - 1].h : ctx->zero_state;
         }
-        // (of one width and over adjacent timesteps: one launch)
+        // (of one width and over adjacent timesteps: one launch, see ReduceArgs)
         bool both = false;
         if (dl == H)
             REINC_TRY(for_runs(lo, hi, nt, {Strip{Ap.data(), dl}, Strip{Mp.data(), H}}, [&](int, int len) {
